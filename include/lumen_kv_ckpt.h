@@ -174,21 +174,23 @@ int lumen_kv_ckpt_plan(const int32_t *d_start, const int32_t *d_end,
  * be NULL only if it is empty (num_blocks, ckpt_rows or bt_cols is 0).
  *
  * Grid size.  The plan's row count lives in device memory, so the launch is
- * sized without it: 384 wavefronts per CU, or 768 when a (row, layer) unit
- * is shorter than 4 KiB (LUMEN_KV_CKPT_WAVES_PER_CU in the environment
- * overrides both), but never more than one per (row, layer) unit that
- * ckpt_rows (or the row range of the _rows calls) could hold, nor more than
- * one per 4 KiB of it when that still leaves 16 per CU.  A checkpoint
- * buffer or window sized to the plan's rows keeps small steps free of idle
- * wavefronts: the pack of an 8-request Llama-3-8B-shaped decode step (65
- * rows) takes 8.4 us into a buffer of its rows and 20-31 us into a
- * multi-step arena, whose size sets the grid.
+ * sized without it.  While ckpt_rows (or the row range of the _rows calls)
+ * is less than 128 MiB of rows and num_reqs at most
+ * LUMEN_KV_CKPT_RANGES_MAX_REQS, the grid is what the chip holds and strides
+ * over the rows that exist.  From there on it has 384 wavefronts per CU, or
+ * 768 when a (row, layer) unit is shorter than 4 KiB
+ * (LUMEN_KV_CKPT_WAVES_PER_CU in the environment overrides both), but never
+ * more than one per (row, layer) unit that ckpt_rows could hold, nor more
+ * than one per 4 KiB of it when that still leaves 16 per CU: a buffer or
+ * window sized to the plan's rows then keeps small steps free of idle
+ * wavefronts.
  *
- * Walk.  A pack of a token-major cache whose token runs (H*D*elem_bytes
- * bytes per layer and K/V) are at most 512 bytes is done page by page: whole
- * page runs are read, and each token's piece is written to its row.  The
- * environment variable LUMEN_KV_CKPT_PAGE_MAJOR=0 or 1 forces this off or
- * on.  The result and the status are the same either way. */
+ * Walk.  Such a larger pack of a token-major cache whose token runs
+ * (H*D*elem_bytes bytes per layer and K/V) are at most 512 bytes is done page
+ * by page: whole page runs are read, and each token's piece is written to its
+ * row.  The environment variable LUMEN_KV_CKPT_PAGE_MAJOR=0 or 1 forces this
+ * off or, at any size and run length, on.  The result and the status are the
+ * same either way. */
 int lumen_kv_ckpt_pack(const lumen_kv_layout *layout, const void *d_cache,
                        const int32_t *d_block_tables, int32_t bt_cols,
                        int32_t num_reqs, void *d_workspace, void *d_ckpt,
@@ -239,14 +241,13 @@ int lumen_kv_ckpt_unpack(const lumen_kv_layout *layout, void *d_cache,
  * lumen_kv_ckpt_pack (or _unpack) over ws, but with no workspace and no
  * plan kernel: each workgroup of the copy scans the ranges (device int32
  * [num_reqs] each) into 8 * (num_reqs + 5) bytes of its LDS, which saves
- * the plan's launch and the wait for it on every call.  The walk is
- * lumen_kv_ckpt_pack's: page by page for a pack of a token-major cache
- * with token runs of at most 512 bytes (for up to 2,048 requests; the
- * page-major walk keeps token and page prefixes, 16 * (num_reqs + 5) bytes
- * of LDS), token by token otherwise.  The grid is sized as for
- * lumen_kv_ckpt_pack; where a (token, layer) unit of the token-major walk
- * is 4 KiB or more, it has half as many wavefronts, each copying two spans
- * of it, so that one scan serves both.
+ * the plan's launch and the wait for it on every call.  The grid is what the
+ * chip holds and strides over the rows that exist, so a step into a large
+ * arena costs what it does into a buffer of its rows (8 requests, 65 rows:
+ * 7.5 us).  Only a pack of a token-major cache with token runs of at most 512
+ * bytes into 4 GiB of rows or more, for up to 2,048 requests, goes page by
+ * page as lumen_kv_ckpt_pack does (its grid is then sized by ckpt_rows, and
+ * it keeps token and page prefixes, 16 * (num_reqs + 5) bytes of LDS).
  *
  * Status.  d_status is a caller-owned device int32, 4-byte aligned.  A call
  * only lowers it (atomic minimum) to the most negative code it records and

@@ -32,12 +32,18 @@
 // of 128-byte lines for the serving shapes, so every access is full-line and
 // no LDS staging is needed for the head-major transpose.
 //
-// Where the walk finds its plan.  Either a plan kernel has written it into
-// a caller's workspace (the row prefix of every request), or the copy
-// reads the token ranges themselves: each workgroup then scans them into
-// LDS before its wavefronts start, which saves the plan kernel's launch and
-// the wait for it; there, where units are long, each wavefront copies two
-// spans so that one scan serves both.
+// That is the span walk (copy_rows_kernel), for large copies over a plan and
+// for host memory.  Two others share its addresses:
+//   * the resident walk (resident_copy_kernel), for smaller copies and for
+//     those that read the token ranges themselves instead of a plan: a grid
+//     of what the chip holds strides over 4 KiB pieces of the rows that
+//     exist, however large the checkpoint buffer is;
+//   * the page-major pack (pack_pages_kernel), for large packs of token-major
+//     caches with short token runs.
+// Where they find their plan: a plan kernel has written it into a caller's
+// workspace (the row prefix of every request), or each workgroup scans the
+// token ranges into LDS before its wavefronts start, which saves the plan
+// kernel's launch and the wait for it.
 
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
@@ -89,18 +95,6 @@ namespace {
 #ifndef LUMEN_KV_CKPT_MIN_WAVES_PER_CU
 #define LUMEN_KV_CKPT_MIN_WAVES_PER_CU 16
 #endif
-// Spans of the copy grid that each wavefront of the one-launch range walk
-// copies when a (row, layer) unit is 4 KiB or more (the grid then has that
-// many times fewer wavefronts than spans; wavefront w takes spans w, w + n,
-// ...).  Each wavefront's set-up scans the ranges, and on the decode
-// workload (4 KiB units, about one unit per span) two spans per wavefront
-// gave 190.7 against 204.6 us per step with one.  With shorter units (2 KiB,
-// head-major Qwen steps, several units per span) two spans per wavefront
-// were slower (703 against 657 us per pack), so those keep one.  Plans
-// read from a workspace set up in a few loads, and keep one span each.
-#ifndef LUMEN_KV_CKPT_RANGE_SPANS_PER_WAVE
-#define LUMEN_KV_CKPT_RANGE_SPANS_PER_WAVE 2
-#endif
 // Double-buffer the batches of a row segment (1) or not (0).
 #ifndef LUMEN_KV_CKPT_PIPELINE
 #define LUMEN_KV_CKPT_PIPELINE 1
@@ -124,6 +118,10 @@ constexpr int kPlanThreads = 1024;
 constexpr int kUnroll = LUMEN_KV_CKPT_UNROLL;
 constexpr int kDefaultWavesPerCU = LUMEN_KV_CKPT_WAVES_PER_CU;
 constexpr int64_t kMinWaveBytes = LUMEN_KV_CKPT_MIN_WAVE_BYTES;
+constexpr int32_t kPieceVecs = kWave * kUnroll;  // resident walk: 4 KiB
+// Requests up to which every wavefront of the resident walk scans the ranges
+// by itself (four per lane).
+constexpr int32_t kFewReqs = 4 * kWave;
 constexpr int64_t kMinWavesPerCU = LUMEN_KV_CKPT_MIN_WAVES_PER_CU;
 
 // Workspace layout (device memory, caller-owned):
@@ -211,12 +209,18 @@ struct Geom {
   int32_t unit_vecs;    // 16-byte vectors per (token, layer): 2*H*D*E/16
   int32_t bt_cols;
   int32_t num_reqs;
-  int64_t spans;        // spans the units are split into (0: one per wave)
   int64_t max_rows;     // rows one launch walks at most: max units / L
   FastDiv div_unit;     // by unit_vecs
   FastDiv div_kv;       // by H*D*E/16, vectors of one (token, layer, K/V)
   FastDiv div_head;     // by D*E/16, vectors of one head
   FastDiv div_bs;       // by block_size
+  // Pieces of a row (resident walk): piece_layers whole layers each, or,
+  // where a layer's unit is longer than a piece, layer_pieces slices of it.
+  int32_t piece_layers;
+  int32_t layer_pieces;
+  int32_t row_pieces;
+  int32_t cus;  // compute units of the device
+  FastDiv div_row_pieces;
 };
 
 __device__ __forceinline__ void record_error(int32_t *err, int code) {
@@ -391,29 +395,18 @@ __device__ __forceinline__ int row_status(bool past, int32_t entry,
   return LUMEN_OK;
 }
 
-// Where the copy walk finds a token row's request, source token and
-// checkpoint row.  WsWalk reads the plan a plan kernel wrote into the
-// workspace; RangeWalk reads the ranges themselves, each workgroup scanning
-// their token counts into LDS, so the copy needs no plan launch before it.  Both give the same rows: the packed rows of request r start at
-// row_base plus the tokens of the valid requests before it; per-request rows
-// start at req_row_base[r] + start[r]; invalid ranges count no tokens.
+// Where the span walk finds a token row's request, source token and
+// checkpoint row: in the plan that a plan kernel wrote into the workspace.
 struct WsWalk {
   const WsHeader *hdr;
   const int64_t *prefix;
   const int64_t *first_row;
   const int32_t *start;
 
-  __device__ __forceinline__ WsWalk(const void *p0, const void *p1,
-                                    const void *p2, const void *p3, int64_t)
-      : hdr(static_cast<const WsHeader *>(p0)),
-        prefix(static_cast<const int64_t *>(p1)),
-        first_row(static_cast<const int64_t *>(p2)),
-        start(static_cast<const int32_t *>(p3)) {}
-
   // Total token rows of the plan; false when the plan does not match the
   // launch (the wavefront then stops).
-  __device__ __forceinline__ bool init(const Geom &g, int lane, int64_t gw,
-                                       int32_t *err, int64_t &total) {
+  __device__ __forceinline__ bool init(const Geom &g, int64_t gw,
+                                       int32_t *err, int64_t &total) const {
     if (hdr->num_reqs != g.num_reqs) {
       if (gw == 0) record_error(err, LUMEN_ERR_INVALID_ARG);
       return false;
@@ -500,134 +493,48 @@ __device__ __forceinline__ int64_t wave_inclusive_sum(int64_t x) {
   return x;
 }
 
+// The same in 32 bits.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int32_t add_dpp(int32_t x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, kCtrl, kRowMask, 0xf, true);
+}
+
+__device__ __forceinline__ int32_t wave_inclusive_sum(int32_t x) {
+  constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+  x = add_dpp<kRowShr + 1, 0xf>(x);
+  x = add_dpp<kRowShr + 2, 0xf>(x);
+  x = add_dpp<kRowShr + 4, 0xf>(x);
+  x = add_dpp<kRowShr + 8, 0xf>(x);
+  x = add_dpp<kRowBcast15, 0xa>(x);
+  x = add_dpp<kRowBcast31, 0xc>(x);
+  return x;
+}
+
 __device__ __forceinline__ bool range_ok(int32_t s, int32_t e) {
   return s >= 0 && e >= s;
 }
 
-// Dynamic LDS of the copy kernel (used by RangeWalk only).
+// Dynamic LDS of the copy kernels that keep a row or page prefix there.
 extern __shared__ __align__(16) int64_t copy_lds[];
 
-struct RangeWalk {
-  const int32_t *start;
-  const int32_t *end;
-  const int64_t *req_row_base;  // null: packed rows from row_base
-  int64_t row_base;
-  // Exclusive prefix of the requests' token counts, prefix[0..R], in LDS:
-  // the workgroup scans the ranges once for its wavefronts.
-  const int64_t *prefix;
-
-  __device__ __forceinline__ RangeWalk(const void *p0, const void *p1,
-                                       const void *p2, const void *,
-                                       int64_t base)
-      : start(static_cast<const int32_t *>(p0)),
-        end(static_cast<const int32_t *>(p1)),
-        req_row_base(static_cast<const int64_t *>(p2)),
-        row_base(base),
-        prefix(copy_lds) {}
-
-  // Thread k of the workgroup sums the token counts of a contiguous chunk
-  // of requests (writing each count to LDS); a wavefront scan and the
-  // wavefronts' totals give each chunk its start; each thread then turns
-  // its counts into prefixes in place.  An invalid range counts no tokens
-  // and is reported once per launch (RANGE), by workgroup 0.
-  __device__ __forceinline__ bool init(const Geom &g, int lane, int64_t,
-                                       int32_t *err, int64_t &total) {
-    int64_t *pre = copy_lds;
-    int64_t *wave_tot = copy_lds + g.num_reqs + 1;  // [kWavesPerBlock]
-    const int tid = threadIdx.x, wave = tid / kWave;
-    const int32_t R = g.num_reqs;
-    const int32_t per = (R + kBlockThreads - 1) / kBlockThreads;
-    const int32_t lo = min(R, tid * per), hi = min(R, lo + per);
-    int64_t local = 0;
-    int bad = 0;
-#pragma unroll 4
-    for (int32_t i = lo; i < hi; ++i) {
-      const int32_t s = start[i], e = end[i];
-      const bool ok = range_ok(s, e);
-      const int64_t n = ok ? int64_t(e) - s : 0;
-      bad |= !ok;
-      pre[i] = n;
-      local += n;
-    }
-    const int64_t incl = wave_inclusive_sum(local);
-    if (lane == kWave - 1) wave_tot[wave] = incl;
-    __syncthreads();
-    int64_t base = 0;
-    total = 0;
-#pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) {
-      const int64_t x = wave_tot[w];
-      if (w < wave) base += x;
-      total += x;
-    }
-    int64_t run = base + incl - local;
-    for (int32_t i = lo; i < hi; ++i) {
-      const int64_t n = pre[i];
-      pre[i] = run;
-      run += n;
-    }
-    if (tid == 0) pre[R] = total;
-    if (__syncthreads_or(bad) && blockIdx.x == 0 && wave == 0)
-      record_error(err, LUMEN_ERR_RANGE);
-    return true;
-  }
-
-  // As WsWalk::locate, over the prefix in LDS.
-  __device__ __forceinline__ void locate(int64_t row, int lane, const Geom &g,
-                                         int32_t &r, int64_t &row_end,
-                                         int64_t &t, int64_t &crow) const {
-    int32_t lo = 0, n = g.num_reqs;
-    while (n > 1) {
-      const int32_t step = (n + kWave - 1) / kWave;
-      const int32_t off = lane * step;
-      const int64_t p = off < n ? prefix[lo + off] : INT64_MAX;
-      const int32_t c = __popcll(__ballot(p <= row));  // >= 1: prefix[lo] <= row
-      lo += (c - 1) * step;
-      n = min(step, n - (c - 1) * step);
-    }
-    r = lo;
-    const int64_t p0 = readlane64(prefix[r], 0);
-    row_end = readlane64(prefix[r + 1], 0);
-    const int32_t s = start[r];
-    t = s + (row - p0);
-    crow = (req_row_base ? req_row_base[r] + s : row_base + p0) +
-           (row - p0) - g.win_first;
-  }
-
-  // As WsWalk::next, over the prefix in LDS.
-  __device__ __forceinline__ void next(int64_t row, const Geom &g,
-                                       int32_t &r2, int64_t &row_end2,
-                                       int64_t &t2, int64_t &crow2) const {
-    do {
-      ++r2;
-    } while (r2 + 1 < g.num_reqs &&
-             readlane64(prefix[r2 + 1], 0) == row + 1);
-    row_end2 = readlane64(prefix[r2 + 1], 0);
-    t2 = start[r2];
-    crow2 = (req_row_base ? req_row_base[r2] + t2 : row_base + row + 1) -
-            g.win_first;
-  }
-};
-
 // One kernel for both directions.  kPack: cache -> checkpoint;
-// otherwise checkpoint -> cache.  The walk's arrays come in as separate
-// __restrict__ arguments (p0..p3, in the order of the walk's constructor):
-// only then may the compiler read them with scalar loads, which the
-// stores of the copy could otherwise clobber.
-template <bool kPack, bool kHeadMajor, class Walk>
+// otherwise checkpoint -> cache.  The plan's arrays come in as separate
+// __restrict__ arguments: only then may the compiler read them with scalar
+// loads, which the stores of the copy could otherwise clobber.
+template <bool kPack, bool kHeadMajor>
 __global__ __launch_bounds__(kBlockThreads) LUMEN_COPY_OCCUPANCY void copy_rows_kernel(
     const uint8_t *__restrict__ src, uint8_t *__restrict__ dst,
-    const int32_t *__restrict__ block_tables, const void *__restrict__ p0,
-    const void *__restrict__ p1, const void *__restrict__ p2,
-    const void *__restrict__ p3, int64_t row_base, int32_t *err, Geom g) {
-  Walk walk(p0, p1, p2, p3, row_base);
+    const int32_t *__restrict__ block_tables, const WsHeader *__restrict__ hdr,
+    const int64_t *__restrict__ prefix, const int64_t *__restrict__ first_row,
+    const int32_t *__restrict__ start, int32_t *err, Geom g) {
+  const WsWalk walk{hdr, prefix, first_row, start};
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int64_t gw = int64_t(blockIdx.x) * kWavesPerBlock + wave;
   const int64_t nw = int64_t(gridDim.x) * kWavesPerBlock;
 
   int64_t total;
-  if (!walk.init(g, lane, gw, err, total)) return;
+  if (!walk.init(g, gw, err, total)) return;
   const int64_t L = g.num_layers;
   const int64_t row_a = min(g.row_lo, total), row_b = min(g.row_hi, total);
   // More rows than a launch walks: refused as a whole (nothing copied).
@@ -636,73 +543,531 @@ __global__ __launch_bounds__(kBlockThreads) LUMEN_COPY_OCCUPANCY void copy_rows_
     return;
   }
   const int64_t units = (row_b - row_a) * L;
-  // The units are split into V equal spans; wave gw copies spans gw,
-  // gw + nw, ... (one span per wave unless the launch asks for fewer waves
-  // than spans, so that each wave's set-up serves several).
-  const int64_t V = g.spans > 0 ? g.spans : nw;
-  for (int64_t v = gw; v < V; v += nw) {
-    int64_t u = row_a * L + units * v / V;
-    const int64_t u_end = row_a * L + units * (v + 1) / V;
-    if (u >= u_end) continue;
+  // Wavefront gw's span.
+  int64_t u = row_a * L + units * gw / nw;
+  const int64_t u_end = row_a * L + units * (gw + 1) / nw;
+  if (u >= u_end) return;
 
-    // First token row of the span and its request.
-    int64_t row = u / L;
-    int32_t l0 = int32_t(u - row * L);
-    int32_t r;
-    int64_t row_end, t, crow;
-    walk.locate(row, lane, g, r, row_end, t, crow);
-    if (g.bt_cols == 0) {  // every page lies past an empty table
-      record_error(err, LUMEN_ERR_RANGE);
-      return;
+  // First token row of the span and its request.
+  int64_t row = u / L;
+  int32_t l0 = int32_t(u - row * L);
+  int32_t r;
+  int64_t row_end, t, crow;
+  walk.locate(row, lane, g, r, row_end, t, crow);
+  if (g.bt_cols == 0) {  // every page lies past an empty table
+    record_error(err, LUMEN_ERR_RANGE);
+    return;
+  }
+  bool past;
+  int32_t b = block_tables[entry_index(r, t, g, past)];
+
+  while (true) {
+    const int32_t nl = int32_t(min(int64_t(g.num_layers - l0), u_end - u));
+    const bool more = u + nl < u_end;
+    const int code = row_status(past, b, crow, g);
+    // Cache side: (block, slot) of layer 0 / K; checkpoint side: the span's
+    // first unit in this row.
+    const uint32_t slot = uint32_t(t) - fdiv(uint32_t(t), g.div_bs) *
+                                            uint32_t(g.block_size);
+    const int64_t cache_tok =
+        int64_t(b) * g.block_bytes + int64_t(slot) * g.slot_bytes;
+    const int64_t ckpt_off =
+        crow * g.row_bytes + int64_t(l0) * g.unit_vecs * 16;
+    // Materialise this row's addresses here: otherwise the compiler sinks
+    // their arithmetic below the next row's block-table load, and the wait
+    // for this row's entry then also waits for that load.
+    asm volatile("" ::"s"(cache_tok), "s"(ckpt_off) : "memory");
+
+    // Position and block-table entry of the next row.  The entry is loaded
+    // unconditionally (clamped index), after every use of this row's entry
+    // and before this row's copy, and first used after that copy: the scalar
+    // load overlaps with the copy instead of stalling the next row.
+    int32_t r2 = r;
+    int64_t row_end2 = row_end, t2 = t + 1, crow2 = crow + 1;
+    if (more && row + 1 == row_end)
+      walk.next(row, g, r2, row_end2, t2, crow2);
+    bool past2;
+    const int32_t b2 = block_tables[entry_index(r2, t2, g, past2)];
+
+    if (code != LUMEN_OK) {
+      record_error(err, code);
+    } else {
+      copy_segment<kPack, kHeadMajor>(src, dst, cache_tok, ckpt_off,
+                                      uint32_t(l0) * uint32_t(g.unit_vecs),
+                                      nl * g.unit_vecs, lane, g);
     }
-    bool past;
-    int32_t b = block_tables[entry_index(r, t, g, past)];
+    if (!more) break;
+    u += nl;
+    l0 = 0;
+    ++row;
+    r = r2;
+    row_end = row_end2;
+    t = t2;
+    crow = crow2;
+    b = b2;
+    past = past2;
+  }
+}
 
-    while (true) {
-      const int32_t nl = int32_t(min(int64_t(g.num_layers - l0), u_end - u));
-      const bool more = u + nl < u_end;
-      const int code = row_status(past, b, crow, g);
-      // Cache side: (block, slot) of layer 0 / K; checkpoint side: the span's
-      // first unit in this row.
-      const uint32_t slot = uint32_t(t) - fdiv(uint32_t(t), g.div_bs) *
-                                              uint32_t(g.block_size);
-      const int64_t cache_tok =
-          int64_t(b) * g.block_bytes + int64_t(slot) * g.slot_bytes;
-      const int64_t ckpt_off =
-          crow * g.row_bytes + int64_t(l0) * g.unit_vecs * 16;
-      // Materialise this row's addresses here: otherwise the compiler sinks
-      // their arithmetic below the next row's block-table load, and the wait
-      // for this row's entry then also waits for that load.
-      asm volatile("" ::"s"(cache_tok), "s"(ckpt_off) : "memory");
+// The workgroup's exclusive prefix of the requests' token counts into LDS,
+// prefix[0..R], and with first_tok each request's first token.  Thread k
+// sums the counts of a contiguous chunk of requests (writing each count to
+// LDS); a wavefront scan and the wavefronts' totals give each chunk its
+// start; each thread then turns its counts into prefixes in place.  An
+// invalid range counts no tokens and is reported once per launch (RANGE), by
+// workgroup 0.  Returns whether a request has more than `most` tokens (the
+// sums may then not fit T).
+template <class T>
+__device__ __forceinline__ bool scan_ranges(const int32_t *start,
+                                            const int32_t *end, int32_t R,
+                                            T *prefix, int32_t *first_tok,
+                                            T *wave_tot, int32_t most,
+                                            int32_t *err, T &total) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int32_t per = (R + kBlockThreads - 1) / kBlockThreads;
+  const int32_t lo = min(R, tid * per), hi = min(R, lo + per);
+  T local = 0;
+  int flags = 0;  // bit 0: an invalid range, bit 1: a long one
+#pragma unroll 4
+  for (int32_t i = lo; i < hi; ++i) {
+    const int32_t s = start[i], e = end[i];
+    const bool ok = range_ok(s, e);
+    const int32_t n = ok ? e - s : 0;
+    flags |= (ok ? 0 : 1) | (n > most ? 2 : 0);
+    prefix[i] = n;
+    if (first_tok) first_tok[i] = s;
+    local += n;
+  }
+  const T incl = wave_inclusive_sum(local);
+  if (lane == kWave - 1) wave_tot[wave] = incl;
+  __syncthreads();
+  T base = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < kWavesPerBlock; ++w) {
+    const T x = wave_tot[w];
+    if (w < wave) base += x;
+    total += x;
+  }
+  T run = base + incl - local;
+  for (int32_t i = lo; i < hi; ++i) {
+    const T n = prefix[i];
+    prefix[i] = run;
+    run += n;
+  }
+  if (tid == 0) prefix[R] = total;
+  const bool bad = __syncthreads_or(flags & 1), big = __syncthreads_or(flags & 2);
+  if (bad && blockIdx.x == 0 && wave == 0) record_error(err, LUMEN_ERR_RANGE);
+  return big;
+}
 
-      // Position and block-table entry of the next row.  The entry is loaded
-      // unconditionally (clamped index), after every use of this row's entry
-      // and before this row's copy, and first used after that copy: the scalar
-      // load overlaps with the copy instead of stalling the next row.
-      int32_t r2 = r;
-      int64_t row_end2 = row_end, t2 = t + 1, crow2 = crow + 1;
-      if (more && row + 1 == row_end)
-        walk.next(row, g, r2, row_end2, t2, crow2);
-      bool past2;
-      const int32_t b2 = block_tables[entry_index(r2, t2, g, past2)];
+// The last index r in [0, n) with pre[r] <= x, one search per lane
+// (pre[0] <= x; equal entries: the last of them, which skips the requests
+// without rows).  Three probes a level: half as many dependent reads as
+// with one.
+template <class T>
+__device__ __forceinline__ int32_t lane_owner(const T *pre, int32_t n, T x) {
+  int32_t r = 0;
+  while (n > 1) {
+    const int32_t q = (n + 3) >> 2, last = n - 1;  // q <= last
+    const T a = pre[r + q], b = pre[r + min(2 * q, last)],
+            c = pre[r + min(3 * q, last)];
+    const int32_t k = int32_t(a <= x) + int32_t(2 * q <= last && b <= x) +
+                      int32_t(3 * q <= last && c <= x);
+    r += k * q;
+    n = min(q, n - k * q);
+  }
+  return r;
+}
 
-      if (code != LUMEN_OK) {
-        record_error(err, code);
+// Piece c of a row: moves the two offsets from the row's start to the
+// piece's, sets where in its layer it starts, and returns its vectors.
+template <bool kSplit>
+__device__ __forceinline__ int32_t piece_at(int32_t c, const Geom &g,
+                                            int64_t &cache_off,
+                                            int64_t &ckpt_off, int32_t &v0) {
+  int32_t layer, nvec;
+  if (kSplit) {
+    layer = c / g.layer_pieces;
+    v0 = (c - layer * g.layer_pieces) * kPieceVecs;
+    nvec = min(kPieceVecs, g.unit_vecs - v0);
+  } else {
+    layer = c * g.piece_layers;
+    v0 = 0;
+    nvec = min(g.piece_layers, g.num_layers - layer) * g.unit_vecs;
+  }
+  cache_off += int64_t(layer) * 2 * g.slab_bytes;
+  ckpt_off += (int64_t(layer) * g.unit_vecs + v0) * 16;
+  return nvec;
+}
+
+// Status and offsets (of the row's start on either side) of token t of
+// request r, `i` rows into the request, for the calling lane.
+__device__ __forceinline__ int row_at(const int32_t *__restrict__ block_tables,
+                                      int32_t r, int64_t t, int64_t crow,
+                                      const Geom &g, int64_t &cache_off,
+                                      int64_t &ckpt_off) {
+  bool past = true;  // every page lies past an empty table
+  int32_t b = -1;
+  if (g.bt_cols > 0) b = block_tables[entry_index(r, t, g, past)];
+  const uint32_t slot =
+      uint32_t(t) - fdiv(uint32_t(t), g.div_bs) * uint32_t(g.block_size);
+  crow -= g.win_first;
+  cache_off = int64_t(b) * g.block_bytes + int64_t(slot) * g.slot_bytes;
+  ckpt_off = crow * g.row_bytes;
+  return row_status(past, b, crow, g);
+}
+
+// Records the most negative code of the wavefront's lanes.
+__device__ __forceinline__ void record_worst(int32_t *err, int code) {
+  if (__ballot(code != LUMEN_OK) == 0) return;
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1)
+    code = min(code, __shfl_xor(code, off, kWave));
+  record_error(err, code);
+}
+
+// Loads or stores one piece: `nv` vectors (at most kPieceVecs) at p, lane_off
+// their offsets on the cache side.
+template <bool kPack>
+__device__ __forceinline__ void load_piece(uint4 (&buf)[kUnroll],
+                                           const uint8_t *__restrict__ p,
+                                           const int64_t (&lane_off)[kUnroll],
+                                           int32_t nv, int lane) {
+#pragma unroll
+  for (int k = 0; k < kUnroll; ++k) {
+    const int32_t v = k * kWave + lane;
+    buf[k] = make_uint4(0, 0, 0, 0);
+    if (v < nv)
+      buf[k] = load16<(nt_policy<kPack>() & 1) != 0>(
+          p + (kPack ? lane_off[k] : int64_t(v) * 16));
+  }
+}
+
+template <bool kPack>
+__device__ __forceinline__ void store_piece(const uint4 (&buf)[kUnroll],
+                                            uint8_t *__restrict__ p,
+                                            const int64_t (&lane_off)[kUnroll],
+                                            int32_t nv, int lane) {
+#pragma unroll
+  for (int k = 0; k < kUnroll; ++k) {
+    const int32_t v = k * kWave + lane;
+    if (v < nv)
+      store16<(nt_policy<kPack>() & 2) != 0>(
+          p + (kPack ? int64_t(v) * 16 : lane_off[k]), buf[k]);
+  }
+}
+
+// Resident walk: the copy for launches whose grid the checkpoint's size does
+// not have to fill.  The host knows how many rows the checkpoint buffer
+// holds, not how many the ranges name, so a grid sized by the buffer is
+// mostly idle workgroups when a few requests append to a large arena, each
+// of which still pays its set-up.  Here the grid is what the chip can hold
+// (kResidentBlocks workgroups per CU) and the workgroups stride over the
+// pieces that exist.
+//
+// A piece is at most kPieceVecs vectors (4 KiB) of one token row: whole
+// layers, so that a lane's offsets on the cache side are the same for every
+// piece and are computed once (kSplit: a slice of one layer whose K and V
+// are longer than that).  In round i, workgroup w copies pieces
+// (i * n + w) * kWavesPerBlock .., one per wavefront, so that at any moment
+// the grid works on a dense window of checkpoint rows.
+//
+// Set-up.  One wavefront of the workgroup scans the ranges and finds the
+// workgroup's next kWave pieces, one per lane (a search of the prefix in
+// LDS, then the block-table entry and the row base), into a table in LDS
+// that all its wavefronts copy from, while the others compute the lanes'
+// offsets: the chain of dependent loads is paid once per 64 pieces, where
+// the span walk pays it per wavefront.  The builder changes from workgroup
+// to workgroup on a CU, to spread it over the SIMDs; later tables are built
+// while the one before is copied.  Everything is in 32 bits; what does not
+// fit (a request of more than 2^30 / num_reqs tokens, or 2^31 pieces: nearly
+// all of their rows are necessarily invalid) takes the slow path, which
+// walks whole rows, one per lane, in 64 bits.
+//
+// What bounds it: small steps the set-up (about 3 us from the start of the
+// kernel to the first copy) and the launch; large ones HBM.  Kernels that
+// copy the same addresses without any plan take 96 us for a gather of 285 MB
+// and 111 us for a scatter of it; the decode step's two copies take 217.
+template <bool kPack, bool kHeadMajor, bool kRanges, bool kSplit>
+__global__ __launch_bounds__(kBlockThreads)
+__attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
+    const uint8_t *__restrict__ src, uint8_t *__restrict__ dst,
+    const int32_t *__restrict__ block_tables, const void *__restrict__ p0,
+    const void *__restrict__ p1, const void *__restrict__ p2,
+    const void *__restrict__ p3, int64_t row_base, int32_t *err, Geom g) {
+  constexpr int kRounds = kWave / kWavesPerBlock;  // rounds per table
+  static_assert(kBlockThreads == kPieceVecs, "one lane offset per thread");
+  __shared__ int64_t tab_cache[2][kWave], tab_ckpt[2][kWave];
+  __shared__ int32_t tab_nvec[2][kWave], tab_v0[2][kWave];
+  __shared__ int64_t offs[kPieceVecs];
+  __shared__ int32_t sh_total;  // rows, or -1: the slow path
+
+  const int32_t R = g.num_reqs;
+  const bool few = R <= kFewReqs;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int builder = (blockIdx.x / g.cus) & (kWavesPerBlock - 1);
+
+  // Ranges: starts, ends, per-request row bases (or null).  Plan: header,
+  // row prefix, each request's first row, starts.
+  const int32_t *start = static_cast<const int32_t *>(kRanges ? p0 : p3);
+  const int64_t *rows_at = static_cast<const int64_t *>(p2);
+  const int32_t *end = static_cast<const int32_t *>(p1);
+  const WsHeader *hdr = static_cast<const WsHeader *>(p0);
+  const int64_t *ws_prefix = static_cast<const int64_t *>(p1);
+
+  int64_t *wave_tot = copy_lds;  // [kWavesPerBlock]
+  int32_t *prefix = reinterpret_cast<int32_t *>(copy_lds + kWavesPerBlock);
+  int32_t *first_tok = prefix + R + 1;
+  const int32_t most = (int32_t(1) << 30) / R;  // tokens of one request
+
+  // Table t of the workgroup, by one wavefront.
+  auto build = [&](int32_t t, int32_t total) {
+    const int32_t row_a = int32_t(min(g.row_lo, int64_t(total)));
+    const int32_t items =
+        (int32_t(min(g.row_hi, int64_t(total))) - row_a) * g.row_pieces;
+    // (below 2^31 + 2^26, so unsigned)
+    const uint32_t mine =
+        (uint32_t(t * kRounds + lane / kWavesPerBlock) * gridDim.x +
+         blockIdx.x) * kWavesPerBlock + lane % kWavesPerBlock;
+    int code = LUMEN_OK;
+    int32_t nvec = 0, v0 = 0;
+    int64_t cache_off = 0, ckpt_off = 0;
+    if (mine < uint32_t(items)) {
+      const uint32_t pr = fdiv(mine, g.div_row_pieces);
+      const int32_t row = row_a + int32_t(pr);
+      const int32_t r = lane_owner(prefix, R, row);
+      const int32_t p = prefix[r], s = first_tok[r];
+      const int64_t first = !kRanges    ? rows_at[r]
+                            : rows_at   ? rows_at[r] + s
+                                        : row_base + p;
+      code = row_at(block_tables, r, int64_t(s) + (row - p), first + (row - p),
+                    g, cache_off, ckpt_off);
+      if (code == LUMEN_OK)
+        nvec = piece_at<kSplit>(int32_t(mine - pr * g.row_pieces), g,
+                                cache_off, ckpt_off, v0);
+    }
+    record_worst(err, code);
+    tab_cache[t & 1][lane] = cache_off;
+    tab_ckpt[t & 1][lane] = ckpt_off;
+    tab_nvec[t & 1][lane] = nvec;
+    if (kSplit) tab_v0[t & 1][lane] = v0;
+  };
+
+  int32_t total;
+  if (few) {
+    if (wave == builder) {
+      constexpr int kPer = kFewReqs / kWave;
+      int32_t n[kPer], local = 0;
+      if (kRanges) {
+        int32_t s[kPer], e[kPer];
+        bool bad = false, big = false;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          const int32_t i = lane * kPer + j;
+          s[j] = i < R ? start[i] : 0;
+          e[j] = i < R ? end[i] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          const bool ok = range_ok(s[j], e[j]);
+          n[j] = ok ? e[j] - s[j] : 0;
+          bad |= !ok;
+          big |= n[j] > most;
+          local += n[j];
+        }
+        const int32_t incl = wave_inclusive_sum(local);
+        int32_t run = incl - local;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          const int32_t i = lane * kPer + j;
+          if (i < R) {
+            prefix[i] = run;
+            first_tok[i] = s[j];
+          }
+          run += n[j];
+        }
+        total = __builtin_amdgcn_readlane(incl, kWave - 1);
+        const bool slow =
+            __ballot(big) != 0 ||
+            int64_t(total) * g.row_pieces >= (int64_t(1) << 31);
+        if (slow)
+          total = -1;
+        else if (blockIdx.x == 0 && __ballot(bad) != 0)
+          record_error(err, LUMEN_ERR_RANGE);
       } else {
-        copy_segment<kPack, kHeadMajor>(src, dst, cache_tok, ckpt_off,
-                                        uint32_t(l0) * uint32_t(g.unit_vecs),
-                                        nl * g.unit_vecs, lane, g);
+        for (int32_t i = lane; i < R; i += kWave) {
+          prefix[i] = int32_t(ws_prefix[i]);
+          first_tok[i] = start[i];
+        }
+        const int64_t rows = hdr->total_rows;
+        total = hdr->num_reqs != R                           ? 0
+                : rows * g.row_pieces >= (int64_t(1) << 31) ||
+                          rows > (int64_t(1) << 30)
+                    ? -1
+                    : int32_t(rows);
+        if (hdr->num_reqs != R && blockIdx.x == 0)
+          record_error(err, LUMEN_ERR_INVALID_ARG);
       }
-      if (!more) break;
-      u += nl;
-      l0 = 0;
-      ++row;
-      r = r2;
-      row_end = row_end2;
-      t = t2;
-      crow = crow2;
-      b = b2;
-      past = past2;
+      if (lane == 0) sh_total = total;
+      if (total > 0) build(0, total);
+    } else {
+      // three wavefronts, four groups of lanes
+      for (int k = (wave - builder - 1) & (kWavesPerBlock - 1);
+           k < kWavesPerBlock; k += kWavesPerBlock - 1)
+        if (!kSplit)
+          offs[k * kWave + lane] =
+              cache_vec_offset<kHeadMajor>(k * kWave + lane, g);
+    }
+    __syncthreads();
+    total = __builtin_amdgcn_readfirstlane(sh_total);
+  } else {
+    if (kRanges) {
+      const bool big = scan_ranges<int32_t>(
+          start, end, R, prefix, first_tok,
+          reinterpret_cast<int32_t *>(wave_tot), most, err, total);
+      total = __builtin_amdgcn_readfirstlane(total);
+      if (big || int64_t(total) * g.row_pieces >= (int64_t(1) << 31))
+        total = -1;
+    } else {
+      for (int32_t i = tid; i < R; i += kBlockThreads) {
+        prefix[i] = int32_t(ws_prefix[i]);
+        first_tok[i] = start[i];
+      }
+      const int64_t rows = hdr->total_rows;
+      total = hdr->num_reqs != R                           ? 0
+              : rows * g.row_pieces >= (int64_t(1) << 31) ||
+                        rows > (int64_t(1) << 30)
+                  ? -1
+                  : int32_t(rows);
+      if (hdr->num_reqs != R && blockIdx.x == 0 && wave == 0)
+        record_error(err, LUMEN_ERR_INVALID_ARG);
+      __syncthreads();
+    }
+    if (!kSplit) offs[tid] = cache_vec_offset<kHeadMajor>(tid, g);
+    if (wave == builder && total > 0) build(0, total);
+    __syncthreads();
+  }
+
+  int64_t lane_off[kUnroll];
+  if (total >= 0) {
+    const int32_t items = (int32_t(min(g.row_hi, int64_t(total))) -
+                           int32_t(min(g.row_lo, int64_t(total)))) *
+                          g.row_pieces;
+    if (!kSplit)
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) lane_off[k] = offs[k * kWave + lane];
+    // Rounds this workgroup has pieces in.
+    const uint32_t per_round = gridDim.x * kWavesPerBlock;
+    const uint32_t wg_first = blockIdx.x * kWavesPerBlock;
+    if (wg_first >= uint32_t(items)) return;
+    const int32_t rounds = (items - 1 - wg_first) / per_round + 1;
+    for (int32_t t = 0;; ++t) {
+      const int32_t left = rounds - t * kRounds;
+      if (wave == builder && left > kRounds) build(t + 1, total);
+      const int32_t cnt = min(left, kRounds);
+      // Piece i of the table; the lane's offsets depend on it only where
+      // pieces are slices of a layer.
+      auto offsets = [&](int32_t i) {
+        if (!kSplit) return;
+        const int32_t v0 = __builtin_amdgcn_readfirstlane(
+            tab_v0[t & 1][i * kWavesPerBlock + wave]);
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+          lane_off[k] = cache_vec_offset<kHeadMajor>(v0 + k * kWave + lane, g);
+      };
+      auto load = [&](uint4 (&buf)[kUnroll], int32_t i) {
+        const int e = i * kWavesPerBlock + wave;
+        if (kPack) offsets(i);
+        load_piece<kPack>(
+            buf,
+            src + readlane64(kPack ? tab_cache[t & 1][e] : tab_ckpt[t & 1][e],
+                             0),
+            lane_off, __builtin_amdgcn_readfirstlane(tab_nvec[t & 1][e]),
+            lane);
+      };
+      auto store = [&](const uint4 (&buf)[kUnroll], int32_t i) {
+        const int e = i * kWavesPerBlock + wave;
+        if (!kPack) offsets(i);
+        store_piece<kPack>(
+            buf,
+            dst + readlane64(kPack ? tab_ckpt[t & 1][e] : tab_cache[t & 1][e],
+                             0),
+            lane_off, __builtin_amdgcn_readfirstlane(tab_nvec[t & 1][e]),
+            lane);
+      };
+      // Double-buffered: the next piece's loads are issued before this
+      // piece's stores.  Memory operations complete in order here, so loads
+      // issued after the stores would wait for the stores to be acknowledged.
+      uint4 a[kUnroll], b[kUnroll];
+      load(a, 0);
+      for (int32_t i = 0; i < cnt; i += 2) {
+        if (i + 1 < cnt) load(b, i + 1);
+        store(a, i);
+        if (i + 1 >= cnt) break;
+        if (i + 2 < cnt) load(a, i + 2);
+        store(b, i + 1);
+      }
+      if (left <= kRounds) break;
+      __syncthreads();  // table t + 1 is there, and table t no longer read
+    }
+    return;
+  }
+
+  // Slow path: rows, one per lane, in 64 bits.
+  int64_t *prefix64 = copy_lds + kWavesPerBlock;
+  int64_t rows64;
+  if (kRanges) {
+    __syncthreads();  // the 32-bit prefix is no longer read
+    scan_ranges<int64_t>(start, end, R, prefix64, nullptr, wave_tot, INT32_MAX,
+                         err, rows64);
+  } else {
+    rows64 = hdr->total_rows;
+  }
+  const int64_t row_a = min(g.row_lo, rows64), row_b = min(g.row_hi, rows64);
+  // More rows than a launch walks: refused as a whole (nothing copied).
+  if (row_b - row_a > g.max_rows) {
+    if (blockIdx.x == 0 && wave == 0) record_error(err, LUMEN_ERR_TOO_MANY);
+    return;
+  }
+  const int64_t gw = int64_t(blockIdx.x) * kWavesPerBlock + wave;
+  const int64_t nw = int64_t(gridDim.x) * kWavesPerBlock;
+  for (int64_t at = row_a + gw * kWave; at < row_b; at += nw * kWave) {
+    const int64_t row = at + lane;
+    int code = LUMEN_OK;
+    bool copy = false;
+    int64_t cache_off = 0, ckpt_off = 0;
+    if (row < row_b) {
+      const int32_t r = kRanges ? lane_owner<int64_t>(prefix64, R, row)
+                                : lane_owner<int64_t>(ws_prefix, R, row);
+      const int64_t p = kRanges ? prefix64[r] : ws_prefix[r];
+      const int32_t s = start[r];
+      const int64_t first = !kRanges    ? rows_at[r]
+                            : rows_at   ? rows_at[r] + s
+                                        : row_base + p;
+      code = row_at(block_tables, r, s + (row - p), first + (row - p), g,
+                    cache_off, ckpt_off);
+      copy = code == LUMEN_OK;
+    }
+    record_worst(err, code);
+    uint64_t todo = __ballot(copy);
+    while (todo) {
+      const int i = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      for (int32_t c = 0; c < g.row_pieces; ++c) {
+        int64_t coff = readlane64(cache_off, i);
+        int64_t koff = readlane64(ckpt_off, i);
+        int32_t v0 = 0;
+        const int32_t nv = piece_at<kSplit>(c, g, coff, koff, v0);
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k)
+          lane_off[k] = cache_vec_offset<kHeadMajor>(v0 + k * kWave + lane, g);
+        uint4 buf[kUnroll];
+        load_piece<kPack>(buf, src + (kPack ? coff : koff), lane_off, nv, lane);
+        store_piece<kPack>(buf, dst + (kPack ? koff : coff), lane_off, nv,
+                           lane);
+      }
     }
   }
 }
@@ -845,7 +1210,7 @@ struct RangePages {
         rows(nullptr),
         items(nullptr) {}
 
-  // As RangeWalk::init, for the token and the page counts at once.
+  // As scan_ranges, for the token and the page counts at once.
   __device__ __forceinline__ bool init(const Geom &g, int64_t,
                                        int32_t *err, int64_t &total,
                                        int64_t &rows_total) {
@@ -1296,7 +1661,7 @@ constexpr int kMaxDevices = 64;
 // (it is a host-side stand-in); each device's address comes from
 // hipGetSymbolAddress at that device's set-up.
 constexpr int32_t kNoAllocMaxReqs = LUMEN_KV_CKPT_NOALLOC_MAX_REQS;
-// The range walk keeps a prefix of 8 bytes per request in each
+// The resident walk keeps a prefix of 8 bytes per request in each
 // workgroup's LDS (32 KiB at the limit).
 constexpr int32_t kRangesMaxReqs = LUMEN_KV_CKPT_RANGES_MAX_REQS;
 constexpr int64_t kMaxUnits = LUMEN_KV_CKPT_MAX_UNITS;
@@ -1308,7 +1673,27 @@ static_assert(sizeof(int64_t) * (2 * (kRangesPageMaxReqs + 1) +
                                  2 * kWavesPerBlock) <= 64 * 1024,
               "page-major range walk LDS");
 static_assert(sizeof(int64_t) * (kRangesMaxReqs + 1 + kWavesPerBlock) <=
-                  64 * 1024, "range walk LDS");
+                  56 * 1024, "resident walk LDS (and about 6 KiB of tables)");
+// Workgroups per CU of the resident walk: what a CU holds at 8 wavefronts
+// per SIMD.  6, 12, 16 and 24 per CU were within 1% on decode steps that
+// fill the chip (217-220 us) and 24 cost small steps 2 us.
+constexpr int64_t kResidentBlocks = 32 / kWavesPerBlock;
+// Copies over a plan take the resident walk while the checkpoint buffer is
+// smaller than this, the span or page-major walk from there on.  Buffers of
+// exactly the plan's rows, resident against the others, us per restore or
+// step: 64 MB 28.1 against 28.4 (one KV head per GPU, 8 x 128, head-major:
+// the same within 2%), 44 MB per copy 40.4 against 40.3; 147 MB 60.5 against
+// 58.3, 380 MB (head-major, fp32) 268 against 258.  Small steps into a larger
+// arena gain in both (23 MB arena: 17.6 to 16.0).
+constexpr int64_t kResidentMaxBytes = int64_t(128) << 20;
+// Copies over the ranges are steps that append to an arena, whatever its
+// size, and take the resident walk: an 8-request step into a 256 MB arena
+// 7.5 us a copy against 26, 256 requests into half of a 1.1 GB arena 217 us
+// a step against 221, into a buffer of exactly their rows 216 against 212,
+// 2 KiB units 286 against 424.  Only a pack of one-KV-head rows (page-major
+// below) of more than this keeps its own walk: there whole contexts are
+// packed, and 114 GB of them run at 6.2 TB/s page by page.
+constexpr int64_t kRangesPageMinBytes = int64_t(4) << 30;
 constexpr size_t kScratchBytes = ws_bytes(kNoAllocMaxReqs);
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 constexpr int32_t kMaxSlots = 64;  // ring slots of a staging pipeline
@@ -1358,11 +1743,12 @@ int waves_per_cu(int64_t unit_bytes) {
                            : kDefaultWavesPerCU;
 }
 
-// Page-major pack for token-major caches whose per-token run is at most
+// Page-major pack for large token-major caches (the sizes are at
+// kResidentMaxBytes and kRangesPageMinBytes) whose per-token run is at most
 // this many bytes (measured on the Llama-3-70B TP=8 shard, 256-byte runs:
 // 6.28 TB/s page-major against 5.35 TB/s token-major).  The environment
 // variable LUMEN_KV_CKPT_PAGE_MAJOR overrides: 0 never, 1 for every
-// token-major pack.
+// token-major pack of any size.
 constexpr int32_t kPageMajorMaxRun = 512;
 
 int page_layers() {
@@ -1374,13 +1760,19 @@ int page_layers() {
   return v;
 }
 
-bool use_page_major(int64_t run_bytes) {
+int page_major_mode() {
   static int mode = [] {
     const char *e = getenv("LUMEN_KV_CKPT_PAGE_MAJOR");
     return e ? atoi(e) : -1;
   }();
-  if (mode == 0) return false;
-  if (mode == 1) return true;
+  return mode;
+}
+
+bool page_major_forced() { return page_major_mode() == 1; }
+
+bool use_page_major(int64_t run_bytes) {
+  if (page_major_mode() == 0) return false;
+  if (page_major_forced()) return true;
   return run_bytes <= kPageMajorMaxRun;
 }
 
@@ -1476,31 +1868,21 @@ Timing take_timing() {
       hipLaunchKernelGGL(kernel, grid, block, lds, s, __VA_ARGS__);          \
   } while (0)
 
-// max_waves > 0 caps the grid (a copy whose checkpoint side is host memory
-// across the host link needs a few hundred wavefronts, not the HBM grid) and
-// keeps the token-major walk, whose checkpoint accesses are sequential.
-template <class Walk>
-void launch_rows(bool pack, bool hnd, unsigned blocks, size_t lds,
-                 hipStream_t s, const Timing &tm, const uint8_t *in,
-                 uint8_t *out, const int32_t *bt, const void *p0,
-                 const void *p1, const void *p2, const void *p3,
-                 int64_t row_base, int32_t *err, const Geom &g) {
-  const dim3 grid(blocks), block(kBlockThreads);
-  if (pack) {
-    if (hnd)
-      LUMEN_LAUNCH(tm, (copy_rows_kernel<true, true, Walk>), grid, block, lds,
-                   s, in, out, bt, p0, p1, p2, p3, row_base, err, g);
-    else
-      LUMEN_LAUNCH(tm, (copy_rows_kernel<true, false, Walk>), grid, block,
-                   lds, s, in, out, bt, p0, p1, p2, p3, row_base, err, g);
-  } else {
-    if (hnd)
-      LUMEN_LAUNCH(tm, (copy_rows_kernel<false, true, Walk>), grid, block,
-                   lds, s, in, out, bt, p0, p1, p2, p3, row_base, err, g);
-    else
-      LUMEN_LAUNCH(tm, (copy_rows_kernel<false, false, Walk>), grid, block,
-                   lds, s, in, out, bt, p0, p1, p2, p3, row_base, err, g);
-  }
+// The span walk's and the resident walk's kernels for a direction and cache
+// order.
+auto span_kernel(bool pack, bool hnd) {
+  return pack ? (hnd ? &copy_rows_kernel<true, true>
+                     : &copy_rows_kernel<true, false>)
+              : (hnd ? &copy_rows_kernel<false, true>
+                     : &copy_rows_kernel<false, false>);
+}
+
+template <bool kRanges, bool kSplit>
+auto resident_kernel(bool pack, bool hnd) {
+  return pack ? (hnd ? &resident_copy_kernel<true, true, kRanges, kSplit>
+                     : &resident_copy_kernel<true, false, kRanges, kSplit>)
+              : (hnd ? &resident_copy_kernel<false, true, kRanges, kSplit>
+                     : &resident_copy_kernel<false, false, kRanges, kSplit>);
 }
 
 // The ranges of a one-launch copy.
@@ -1563,6 +1945,19 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
   g.div_kv = make_fastdiv(uint32_t(H * d_bytes / 16));
   g.div_head = make_fastdiv(uint32_t(d_bytes / 16));
   g.div_bs = make_fastdiv(uint32_t(bs));
+  if (g.unit_vecs <= kPieceVecs) {
+    g.layer_pieces = 1;
+    g.piece_layers = kPieceVecs / g.unit_vecs;
+    if (g.piece_layers > g.num_layers) g.piece_layers = g.num_layers;
+    g.row_pieces = (g.num_layers + g.piece_layers - 1) / g.piece_layers;
+  } else {
+    // (a row has fewer than 2^31 vectors, so no product here overflows)
+    g.layer_pieces = (g.unit_vecs - 1) / kPieceVecs + 1;
+    g.piece_layers = 1;
+    g.row_pieces = g.num_layers * g.layer_pieces;
+  }
+  g.div_row_pieces = make_fastdiv(uint32_t(g.row_pieces));
+  g.cus = dev->cus;
 
   WsView v = ranges ? WsView{} : ws_view(ws, num_reqs);
   int32_t *err = err_word ? err_word : &v.hdr->err;
@@ -1589,17 +1984,6 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
     if (pieces < waves) waves = pieces > 0 ? pieces : 1;
   }
   const unsigned blocks = unsigned((waves + kWavesPerBlock - 1) / kWavesPerBlock);
-  // Token-major walk over the ranges: `waves` spans, several of them per
-  // wavefront for long units.
-  unsigned row_blocks = blocks;
-  g.spans = 0;
-  const int64_t spw = LUMEN_KV_CKPT_RANGE_SPANS_PER_WAVE;
-  if (ranges && spw > 1 && g.row_bytes / lay->num_layers >= 4096 &&
-      waves >= 2 * spw) {
-    g.spans = waves;
-    const int64_t phys = (waves + spw - 1) / spw;
-    row_blocks = unsigned((phys + kWavesPerBlock - 1) / kWavesPerBlock);
-  }
   hipStream_t s = static_cast<hipStream_t>(stream);
   const uint8_t *in = static_cast<const uint8_t *>(src);
   uint8_t *out = static_cast<uint8_t *>(dst);
@@ -1608,7 +1992,19 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
   const bool page_major = pack && !hnd && row_lo == 0 &&
                           row_hi == INT64_MAX && win_first == 0 &&
                           max_waves == 0 && use_page_major(H * d_bytes);
-  if (ranges && page_major && num_reqs <= kRangesPageMaxReqs) {
+  // The resident walk, or a walk whose grid the buffer sizes.
+  const int64_t cap_bytes = cap_rows <= (INT64_MAX / 2) / g.row_bytes
+                                ? cap_rows * g.row_bytes
+                                : INT64_MAX;
+  const bool pages =
+      page_major &&
+      (page_major_forced() ||
+       cap_bytes >= (ranges ? kRangesPageMinBytes : kResidentMaxBytes)) &&
+      (!ranges || num_reqs <= kRangesPageMaxReqs);
+  const bool resident =
+      !pages && (ranges || (max_waves == 0 && num_reqs <= kRangesMaxReqs &&
+                            cap_bytes < kResidentMaxBytes));
+  if (ranges && pages) {
     // LDS: the token and page prefixes, [R + 1] each, and the wavefronts'
     // totals of both.
     const size_t lds =
@@ -1617,13 +2013,33 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
                  dim3(kBlockThreads), lds, s, in, out, bt, ranges->start,
                  ranges->end, ranges->req_row_base, nullptr, nullptr,
                  ranges->row_base, err, g);
-  } else if (ranges) {
-    // LDS: prefix[R + 1] and the wavefronts' totals.
+  } else if (resident) {
+    // LDS: the wavefronts' totals and prefix[R + 1], in 64 bits or, with each
+    // request's first token, in 32.
     const size_t lds = sizeof(int64_t) * (size_t(num_reqs) + 1 + kWavesPerBlock);
-    launch_rows<RangeWalk>(pack, hnd, row_blocks, lds, s, tm, in, out, bt,
-                           ranges->start, ranges->end, ranges->req_row_base,
-                           nullptr, ranges->row_base, err, g);
-  } else if (page_major) {
+    // No more workgroups than the buffer holds pieces for.
+    int64_t wgs = int64_t(dev->cus) * kResidentBlocks;
+    if (cap_rows < wgs * kWavesPerBlock) {
+      const int64_t need =
+          (cap_rows * g.row_pieces + kWavesPerBlock - 1) / kWavesPerBlock;
+      if (need < wgs) wgs = need > 0 ? need : 1;
+    }
+    const bool split = g.layer_pieces > 1;
+    const dim3 grid{unsigned(wgs)}, block{kBlockThreads};
+    if (ranges)
+      LUMEN_LAUNCH(tm,
+                   (split ? resident_kernel<true, true>(pack, hnd)
+                          : resident_kernel<true, false>(pack, hnd)),
+                   grid, block, lds, s, in, out, bt, ranges->start,
+                   ranges->end, ranges->req_row_base, nullptr,
+                   ranges->row_base, err, g);
+    else
+      LUMEN_LAUNCH(tm,
+                   (split ? resident_kernel<false, true>(pack, hnd)
+                          : resident_kernel<false, false>(pack, hnd)),
+                   grid, block, lds, s, in, out, bt, v.hdr, v.prefix,
+                   v.first_row, v.start, 0, err, g);
+  } else if (pages) {
     hipLaunchKernelGGL(item_scan_kernel, dim3(1), dim3(kPlanThreads), 0, s,
                        v.hdr, v.prefix, v.start, v.items, num_reqs,
                        lay->block_size);
@@ -1631,8 +2047,9 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
                  dim3(kBlockThreads), 0, s, in, out, bt, v.hdr, v.prefix,
                  v.first_row, v.start, v.items, 0, err, g);
   } else {
-    launch_rows<WsWalk>(pack, hnd, row_blocks, 0, s, tm, in, out, bt, v.hdr,
-                        v.prefix, v.first_row, v.start, 0, err, g);
+    LUMEN_LAUNCH(tm, span_kernel(pack, hnd), dim3(blocks),
+                 dim3(kBlockThreads), 0, s, in, out, bt, v.hdr, v.prefix,
+                 v.first_row, v.start, err, g);
   }
   return hipGetLastError() == hipSuccess ? LUMEN_OK : LUMEN_ERR_HIP;
 }

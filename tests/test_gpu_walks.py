@@ -1,0 +1,182 @@
+"""The walks of the copy kernels at the sizes where their rules change hands:
+the resident walk around its edges (pieces of whole layers, slices of a long
+layer, requests scanned by one wavefront or by the workgroup, tables that are
+refilled, the slow path), and the page-major and span walks at small sizes,
+which a process reaches by the environment or through a plan of many
+requests.  Every result is compared with the CPU oracle, bit for bit."""
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_17787_amd.kvckpt as kv
+from paper_2606_17787_amd import workloads as W
+from paper_2606_17787_amd.workloads import CacheShape, HND, NHD
+
+from gpu_util import assert_same, dev, gpu_path, h2d, oracle_path
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    # one piece per row, several layers each; the last piece is shorter
+    "layers-per-piece": CacheShape(5, 1, 128, 16, NHD),
+    "layers-per-piece-hnd": CacheShape(7, 2, 64, 8, HND, 1),
+    # a unit of exactly one piece (256 vectors), and one vector either side
+    "unit-256": CacheShape(3, 8, 128, 16, NHD),
+    "unit-254": CacheShape(3, 1, 1016, 4, NHD),
+    "unit-258": CacheShape(3, 1, 1032, 4, NHD),
+    # slices of a layer, K and V meeting inside one
+    "slices": CacheShape(2, 3, 480, 4, NHD, 4),
+    "slices-hnd": CacheShape(2, 8, 128, 8, HND, 4),
+    # the shortest unit
+    "unit-2": CacheShape(3, 1, 16, 3, NHD, 1),
+}
+
+
+def ranges_case(shape, R, seed, max_tok=40, longest=9):
+    rng = np.random.default_rng(seed)
+    bs = shape.block_size
+    cols = -(-max_tok // bs)
+    nb = R * cols + 3
+    bt = rng.permutation(nb).astype(np.int32)[:R * cols].reshape(R, cols)
+    bt2 = rng.permutation(nb).astype(np.int32)[:R * cols].reshape(R, cols)
+    s = rng.integers(0, max_tok, R).astype(np.int32)
+    e = np.minimum(s + rng.integers(0, longest, R), max_tok).astype(np.int32)
+    src = W.random_words(rng, shape.pool_elems(nb), shape.elem_bytes)
+    dst = W.random_words(rng, shape.pool_elems(nb), shape.elem_bytes)
+    return nb, bt, bt2, s, e, src, dst
+
+
+@pytest.mark.parametrize("via", ["plan", "ranges"])
+@pytest.mark.parametrize("R", [1, 3, 64, 255, 256, 257, 700])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_resident_walk_matches_oracle(name, R, via):
+    shape = SHAPES[name]
+    nb, bt, bt2, s, e, src, dst = ranges_case(shape, R, R * 7 + len(name))
+    if R == 1:
+        s[0], e[0] = 3, 31
+    ref = oracle_path(shape, nb, src, bt, s, e, nb, dst.copy(), bt2)
+    got = gpu_path(shape, nb, src, bt, s, e, nb, dst, bt2, via=via)
+    assert_same(got, ref, f"{name} R={R} {via}")
+
+
+@pytest.mark.parametrize("via", ["plan", "ranges"])
+@pytest.mark.parametrize("name", ["layers-per-piece", "slices-hnd"])
+def test_resident_walk_fills_its_table_again(name, via):
+    """More pieces than the resident grid's first tables hold (64 per
+    workgroup): 2,100 workgroups' worth, into a buffer of exactly the rows
+    and into an arena with a row base."""
+    shape = SHAPES[name]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    unit = 2 * shape.num_kv_heads * shape.head_dim * shape.elem_bytes // 16
+    per_row = (-(-shape.num_layers // max(1, 256 // unit)) if unit <= 256
+               else shape.num_layers * -(-unit // 256))
+    rows = -(-(8 * cus * 64 + 4 * 8 * cus * 3 + 5) // per_row)
+    R = 37
+    n = np.full(R, rows // R + 1, np.int64)
+    bs = shape.block_size
+    cols = int(-(-n.max() // bs))
+    rng = np.random.default_rng(5)
+    nb = 97  # shared blocks: many requests read, and write, the same ones
+    bt = rng.integers(0, nb, (R, cols)).astype(np.int32)
+    s, e = np.zeros(R, np.int32), n.astype(np.int32)
+    src = W.random_words(rng, shape.pool_elems(nb), shape.elem_bytes)
+    base = 11
+    st, want = oracle.pack(shape, nb, src, bt, s, e, base, None)
+    assert st == 0
+    got = gpu_path(shape, nb, src, bt, s, e, row_base=base, via=via)
+    assert got[0] == 0 and np.array_equal(got[1][base:], want[base:])
+    # the unpack writes the pack's own rows back into the same blocks
+    d = h2d(src)
+    ck = h2d(want)
+    status = torch.zeros(1, dtype=torch.int32, device=dev())
+    if via == "ranges":
+        kv.lumen_kv_ckpt_unpack_ranges(shape, nb, d, h2d(bt), h2d(s), h2d(e),
+                                       ck.view(-1), status, base)
+    else:
+        ws = kv.new_workspace(R, dev())
+        kv.lumen_kv_ckpt_plan(h2d(s), h2d(e), ws, base)
+        kv.lumen_kv_ckpt_unpack(shape, nb, d, h2d(bt), ws, ck.view(-1))
+        assert kv.lumen_kv_ckpt_status(ws) == 0
+    assert int(status.item()) == 0
+    assert torch.equal(d, h2d(src))
+
+
+@pytest.mark.parametrize("R", [2, 256, 300, 4096])
+def test_slow_path_copies_the_valid_rows(R):
+    """A request of more tokens than the 32-bit path takes (2^30 / R), of
+    which only the first lie in its block table: the valid rows of every
+    request are copied, the others are RANGE errors."""
+    shape = CacheShape(2, 2, 16, 4, NHD)
+    bs, cols = shape.block_size, 2
+    s = np.zeros(R, np.int32)
+    e = np.full(R, 1, np.int32)
+    long = min(2**31 - 1, (1 << 30) // R + 1)
+    e[R // 2] = long
+    rng = np.random.default_rng(R)
+    nb = 2 * R
+    bt = rng.permutation(nb).astype(np.int32).reshape(R, cols)
+    src = W.random_bits(rng, shape.pool_elems(nb))
+    rows = R // 2 + bs * cols + 4  # the long request's rows push the rest out
+    valid = np.ones(R, np.int32)
+    valid[R // 2] = bs * cols
+    st, want = oracle.pack(shape, nb, src, bt[:R // 2 + 1], s[:R // 2 + 1],
+                           valid[:R // 2 + 1])
+    assert st == 0
+    st_o = kv.LUMEN_ERR_CAPACITY if R // 2 + 1 < R else kv.LUMEN_ERR_RANGE
+    for via in ("plan", "ranges"):
+        got = gpu_path(shape, nb, src, bt, s, e, ckpt_rows=rows, via=via)
+        assert got[0] == st_o
+        n = R // 2 + bs * cols
+        assert np.array_equal(got[1][:n], want)
+        assert (got[1][n:] == 0x5A).all()
+
+
+def test_plan_of_many_requests_takes_the_span_walk():
+    """More requests than the resident walk takes: 4,097, pack and unpack of
+    a token-major and a head-major cache."""
+    for order in (NHD, HND):
+        shape = CacheShape(2, 4, 64, 8, order)
+        R = 4097
+        nb, bt, bt2, s, e, src, dst = ranges_case(shape, R, 9, 16, 3)
+        ref = oracle_path(shape, nb, src, bt, s, e, nb, dst.copy(), bt2)
+        got = gpu_path(shape, nb, src, bt, s, e, nb, dst, bt2, via="plan")
+        assert_same(got, ref, order)
+
+
+FORCED = """
+import sys
+sys.path.insert(0, {root!r}); sys.path.insert(0, {tests!r})
+import test_gpu_parity as P, test_gpu_walks as T
+for via in ("plan", "ranges"):
+    for R in (1, 5, 300):
+        for name in ("layers-per-piece", "unit-254", "unit-2"):
+            T.test_resident_walk_matches_oracle(name, R, via)
+            print(via, R, name, flush=True)
+    for case in range(len(P.ERROR_CASES)):
+        P.test_error_inputs_still_copy_every_valid_row(case, "nhd-page-major",
+                                                       via)
+    P.test_ranges_past_the_unit_limit_copy_nothing("nhd-page-major", via)
+    P.test_long_invalid_ranges_still_copy_their_valid_rows("nhd-page-major",
+                                                           via)
+    P.test_reduced_tp8_shard_in_place(via)
+    print(via, "errors", flush=True)
+print("forced walks ok", flush=True)
+"""
+
+
+def test_page_major_walk_at_small_sizes():
+    """The page-major pack, forced by the environment on caches far below the
+    size it is chosen from, in a process of its own (the library reads the
+    variable once)."""
+    tests = os.path.dirname(os.path.abspath(__file__))
+    code = FORCED.format(root=os.path.dirname(tests), tests=tests)
+    out = subprocess.run([sys.executable, "-u", "-c", code],
+                         env=dict(os.environ, LUMEN_KV_CKPT_PAGE_MAJOR="1"),
+                         capture_output=True, text=True, timeout=110)
+    assert out.returncode == 0 and "forced walks ok" in out.stdout, \
+        out.stdout[-2000:] + out.stderr[-2000:]
