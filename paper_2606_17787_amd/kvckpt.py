@@ -146,28 +146,34 @@ def layout(shape, num_blocks: int) -> lumen_kv_layout:
                            getattr(shape, "elem_bytes", 2), order)
 
 
-# Small checkpoints are launch-bound, so the per-call marshalling below is
-# kept cheap.
-def _stream_handle(stream: Optional[torch.cuda.Stream]):
+# Small checkpoints are launch-bound, and a launch takes the host 3 us in the
+# library: the marshalling below is kept well under that.  Pointers and stream
+# handles are passed as integers (the argument types convert them), and the
+# current device is read without torch.cuda.current_device's initialisation
+# check, which a tensor on a device has been through.
+_current_device = torch._C._cuda_getDevice
+_current_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
+def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
     if stream is not None:
-        return ctypes.c_void_p(stream.cuda_stream)
+        return stream.cuda_stream
     # the raw handle of the current stream, without building a Stream object
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(
-        torch.cuda.current_device()))
+    return _current_raw_stream(torch.cuda.current_device())
 
 
-def _required_stream(stream) -> ctypes.c_void_p:
+def _required_stream(stream) -> int:
     if not isinstance(stream, torch.cuda.Stream):
         raise ValueError("the staging pipelines need explicit streams "
                          "(torch.cuda.Stream); see their docstrings")
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
-def _dev(t: torch.Tensor, what: str, dtype=None) -> ctypes.c_void_p:
+def _dev(t: torch.Tensor, what: str, dtype=None) -> int:
     d = t.get_device()
     if d < 0:
         raise ValueError(f"{what} must be a device tensor")
-    if d != torch.cuda.current_device():
+    if d != _current_device():
         # the library launches on the current device
         raise ValueError(f"{what} is on cuda:{d}, the current device is "
                          f"cuda:{torch.cuda.current_device()}")
@@ -175,7 +181,7 @@ def _dev(t: torch.Tensor, what: str, dtype=None) -> ctypes.c_void_p:
         raise ValueError(f"{what} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{what} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _check(code: int, where: str):
@@ -317,13 +323,15 @@ class PreparedCall:
         self._keep = keep
 
     def __call__(self, stream: Optional[torch.cuda.Stream] = None) -> None:
-        if torch.cuda.current_device() != self._device:
+        d = self._device
+        if _current_device() != d:
             raise ValueError(f"{self._name} was prepared on "
-                             f"cuda:{self._device}; the current device is "
+                             f"cuda:{d}; the current device is "
                              f"cuda:{torch.cuda.current_device()}")
-        h = (stream.cuda_stream if stream is not None else
-             torch._C._cuda_getCurrentRawStream(self._device))
-        _check(self._fn(*self._args, ctypes.c_void_p(h)), self._name)
+        code = self._fn(*self._args, _current_raw_stream(d)
+                        if stream is None else stream.cuda_stream)
+        if code:
+            raise LumenError(code, self._name)
 
 
 def prepare_plan(start: torch.Tensor, end: torch.Tensor,
