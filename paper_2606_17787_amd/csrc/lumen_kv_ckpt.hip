@@ -1519,13 +1519,18 @@ __global__ __launch_bounds__(kBlockThreads) void validate_kernel(
   }
 }
 
-// Draft-state alignment, step 1: one wavefront per request (grid-strided)
-// finds the first position where the draft and committed tokens differ,
-// 1024 positions per round, truncates the request's KV length to it, and
-// counts the allocated table entries of the pages the shorter KV no longer
-// reaches.  Per request it leaves in the workspace the count (-1 for a
-// request with inconsistent lengths, which is left unchanged) and the page
-// span [lo, hi) packed into one int64.
+// Draft-state alignment, step 1: one workgroup per request (grid-strided)
+// finds the first position where the draft and committed tokens differ, 4096
+// positions per round (1024 per wavefront, 16 per lane, all loads in flight
+// together), truncates the request's KV length to it, and counts the
+// allocated table entries of the pages the shorter KV no longer reaches.  Per
+// request it leaves in the workspace the count (-1 for a request with
+// inconsistent lengths, which is left unchanged) and the page span [lo, hi)
+// packed into one int64.  A histories' compare is bound by latency, not by
+// its bytes: a wavefront per request took a round trip per 1024 tokens of the
+// longest history.
+constexpr int kMatch = 16;  // positions per lane and round
+
 __global__ __launch_bounds__(kBlockThreads) void draft_match_kernel(
     const int32_t *__restrict__ draft, int32_t draft_cols,
     const int32_t *__restrict__ draft_len,
@@ -1534,67 +1539,88 @@ __global__ __launch_bounds__(kBlockThreads) void draft_match_kernel(
     const int32_t *__restrict__ block_tables, int32_t bt_cols,
     int32_t block_size, int32_t num_reqs, int32_t *replay, int64_t *count,
     int64_t *span) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int64_t gw = int64_t(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
-  const int64_t nw = int64_t(gridDim.x) * kWavesPerBlock;
-  for (int64_t r = gw; r < num_reqs; r += nw) {
+  __shared__ int32_t first_diff[2];  // by round, alternately
+  __shared__ int32_t entries;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  for (int64_t r = blockIdx.x; r < num_reqs; r += gridDim.x) {
     const int32_t dl = draft_len[r], cl = committed_len[r], kl = kv_len[r];
     if (dl < 0 || cl < 0 || kl < 0 || dl > draft_cols ||
         cl > committed_cols || int64_t(kl) > int64_t(bt_cols) * block_size) {
-      if (lane == 0) {
+      if (tid == 0) {
         count[r] = -1;
         span[r] = 0;
         replay[r] = 0;
       }
       continue;
     }
+    if (tid == 0) {
+      first_diff[0] = INT32_MAX;
+      entries = 0;
+    }
+    __syncthreads();
     const int32_t lim = min(dl, cl);
     const int32_t *d = draft + r * draft_cols;
     const int32_t *c = committed + r * committed_cols;
-    // kMatch positions per lane per round, all loads in flight together;
-    // the round's first mismatch is the minimum over the lanes.
-    constexpr int kMatch = 16;
     int32_t p = lim;
-    for (int32_t base = 0; base < lim; base += kWave * kMatch) {
+    // (64-bit: a round's end may pass INT32_MAX)
+    int64_t base = 0;
+    for (int round = 0; base < lim; base += kBlockThreads * kMatch, ++round) {
+      const int64_t at = base + wave * (kWave * kMatch) + lane;
       int32_t dv[kMatch], cv[kMatch];
 #pragma unroll
       for (int k = 0; k < kMatch; ++k) {
-        const int32_t i = base + k * kWave + lane;
+        const int64_t i = at + k * kWave;
         dv[k] = i < lim ? d[i] : 0;
         cv[k] = i < lim ? c[i] : 0;
       }
       int32_t mine = INT32_MAX;
 #pragma unroll
       for (int k = kMatch - 1; k >= 0; --k)
-        if (dv[k] != cv[k]) mine = base + k * kWave + lane;
-#pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1)
-        mine = min(mine, __shfl_xor(mine, off, kWave));
-      if (mine != INT32_MAX) {  // wave-uniform after the reduction
-        p = mine;
+        if (dv[k] != cv[k]) mine = int32_t(at + k * kWave);
+      if (mine != INT32_MAX) atomicMin(&first_diff[round & 1], mine);
+      __syncthreads();
+      const int32_t found = first_diff[round & 1];
+      if (found != INT32_MAX) {  // the same for every thread
+        p = found;
         break;
       }
+      if (tid == 0) first_diff[(round + 1) & 1] = INT32_MAX;
+      __syncthreads();
     }
     const int32_t valid = min(kl, p);
-    const int32_t lo = (valid + block_size - 1) / block_size;
-    const int32_t hi = (kl + block_size - 1) / block_size;
-    int64_t n = 0;
+    const int32_t lo = int32_t((int64_t(valid) + block_size - 1) / block_size);
+    const int32_t hi = int32_t((int64_t(kl) + block_size - 1) / block_size);
     const int32_t *row = block_tables + r * bt_cols;
-    for (int32_t j = lo + lane; j - lane < hi; j += kWave)
-      n += __popcll(__ballot(j < hi && row[j] >= 0));
-    if (lane == 0) {
+    // (few pages at most: counted by one wavefront where they fit it)
+    int64_t n = 0;
+    if (hi - lo <= kWave) {
+      if (wave == 0)
+        n = __popcll(__ballot(lo + lane < hi && row[lo + lane] >= 0));
+    } else {
+      int32_t mine = 0;
+      for (int32_t j = lo + tid; j < hi; j += kBlockThreads)
+        mine += row[j] >= 0;
+      if (mine != 0) atomicAdd(&entries, mine);
+      __syncthreads();
+      n = entries;
+    }
+    if (tid == 0) {
       kv_len[r] = valid;
       replay[r] = cl - valid;
       count[r] = n;
       span[r] = (int64_t(lo) << 32) | int64_t(hi);
     }
+    __syncthreads();  // the next request's first_diff and entries
   }
 }
 
 // Draft-state alignment, step 2: one workgroup scans the per-request counts
 // (as the row plan does), lists the freed block ids in request order, then
 // page order, clears their table entries, and writes the status of this
-// call into the workspace's error word (a new epoch).
+// call into the workspace's error word (a new epoch).  Up to kPlanThreads
+// requests a thread has one of them, whose span and first entry it reads
+// beside its count, before the scan.
 __global__ __launch_bounds__(kPlanThreads) void draft_free_kernel(
     int32_t *block_tables, int32_t bt_cols, int32_t R,
     const int64_t *__restrict__ count, const int64_t *__restrict__ span,
@@ -1602,7 +1628,6 @@ __global__ __launch_bounds__(kPlanThreads) void draft_free_kernel(
     WsHeader *hdr) {
   constexpr int kWaves = kPlanThreads / kWave;
   __shared__ int64_t wave_sum[kWaves];
-  __shared__ int bad;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wid = tid / kWave;
@@ -1611,37 +1636,41 @@ __global__ __launch_bounds__(kPlanThreads) void draft_free_kernel(
   const int32_t hi = min(R, lo + per);
   int64_t local = 0;
   int my_bad = 0;
-  for (int32_t i = lo; i < hi; ++i) {
-    const int64_t n = count[i];
-    if (n < 0) my_bad = 1; else local += n;
-  }
-  int64_t x = local;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int64_t y = __shfl_up(x, d, kWave);
-    if (lane >= d) x += y;
-  }
-  if (lane == kWave - 1) wave_sum[wid] = x;
-  if (tid == 0) bad = 0;
-  __syncthreads();
-  if (my_bad) atomicOr(&bad, 1);
-  if (wid == 0) {
-    int64_t v = lane < kWaves ? wave_sum[lane] : 0;
-#pragma unroll
-    for (int d = 1; d < kWaves; d <<= 1) {
-      const int64_t y = __shfl_up(v, d, kWave);
-      if (lane >= d) v += y;
+  int64_t span0 = 0;
+  int32_t blk0 = -1;
+  if (per == 1 && lo < hi) {
+    const int64_t n = count[lo];
+    span0 = span[lo];
+    if (n < 0)
+      my_bad = 1;
+    else
+      local = n;
+    if (n > 0)
+      blk0 = block_tables[int64_t(lo) * bt_cols + int32_t(span0 >> 32)];
+  } else {
+    for (int32_t i = lo; i < hi; ++i) {
+      const int64_t n = count[i];
+      if (n < 0) my_bad = 1; else local += n;
     }
-    if (lane < kWaves) wave_sum[lane] = v;
   }
-  __syncthreads();
-  int64_t off = (wid > 0 ? wave_sum[wid - 1] : 0) + x - local;  // exclusive
+  const int64_t x = wave_inclusive_sum(local);
+  if (lane == kWave - 1) wave_sum[wid] = x;
+  const int bad = __syncthreads_or(my_bad);
+  int64_t before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const int64_t y = wave_sum[w];
+    if (w < wid) before += y;
+    total += y;
+  }
+  int64_t off = before + x - local;  // exclusive
   for (int32_t i = lo; i < hi; ++i) {
-    if (count[i] <= 0) continue;
-    const int32_t a = int32_t(span[i] >> 32), b = int32_t(span[i] & 0xffffffff);
+    if ((per == 1 ? local : count[i]) <= 0) continue;
+    const int64_t sp = per == 1 ? span0 : span[i];
+    const int32_t a = int32_t(sp >> 32), b = int32_t(sp & 0xffffffff);
     int32_t *row = block_tables + int64_t(i) * bt_cols;
     for (int32_t j = a; j < b; ++j) {
-      const int32_t blk = row[j];
+      const int32_t blk = per == 1 && j == a ? blk0 : row[j];
       if (blk < 0) continue;
       if (off < freed_cap) {  // an entry is cleared only once it is listed
         freed[off] = blk;
@@ -1651,7 +1680,6 @@ __global__ __launch_bounds__(kPlanThreads) void draft_free_kernel(
     }
   }
   if (tid == 0) {
-    const int64_t total = wave_sum[kWaves - 1];
     *freed_count = total;
     hdr->total_rows = 0;  // no copy plan in the workspace any more
     hdr->num_reqs = -1;
@@ -2620,8 +2648,8 @@ int lumen_kv_draft_align(const int32_t *d_draft, int32_t draft_cols,
   hipStream_t s = static_cast<hipStream_t>(stream);
   clear_pending_error();
   if (num_reqs > 0) {
-    int64_t blocks = (int64_t(num_reqs) + kWavesPerBlock - 1) / kWavesPerBlock;
-    const int64_t cap = int64_t(dev->cus) * 8;
+    int64_t blocks = num_reqs;
+    const int64_t cap = int64_t(dev->cus) * 32;
     if (blocks > cap) blocks = cap;
     hipLaunchKernelGGL(draft_match_kernel, dim3(unsigned(blocks)),
                        dim3(kBlockThreads), 0, s, d_draft, draft_cols,
