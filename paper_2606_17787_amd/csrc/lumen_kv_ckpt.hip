@@ -13,8 +13,8 @@
 // (token row, layer): one unit is the K and V of one token in one layer,
 // 2*H*D*E bytes, contiguous on the checkpoint side.  Units are numbered in
 // checkpoint order, u = packed_row * L + layer, and the grid's wavefronts
-// split [0, total_units) into equal contiguous spans, so every wavefront
-// moves the same number of bytes whatever the mix of request lengths.  The
+// take equal contiguous spans of [0, total_units), so every wavefront that
+// has one moves the same bytes whatever the mix of request lengths.  The
 // grid is oversubscribed (hundreds of wavefronts per CU, about one unit each
 // on a decode step): wavefronts that share a workload still run at very
 // different speeds on this chip, and short-lived ones let the hardware
@@ -543,9 +543,15 @@ __global__ __launch_bounds__(kBlockThreads) LUMEN_COPY_OCCUPANCY void copy_rows_
     return;
   }
   const int64_t units = (row_b - row_a) * L;
-  // Wavefront gw's span.
-  int64_t u = row_a * L + units * gw / nw;
-  const int64_t u_end = row_a * L + units * (gw + 1) / nw;
+  // Wavefront gw's span: every wavefront that has one gets as many units, so
+  // that a plan which does not fill the buffer keeps the first wavefronts of
+  // the grid busy and the idle ones drain behind them.  Dealt evenly over the
+  // grid instead, 256 requests in half of their regions took 230 us a step
+  // against 224, a 196-row step in a 704 MB arena 52 against 48; full buffers
+  // are the same within 0.4%, or up to 4% faster (1 GB in 4 KiB units).
+  const int64_t per = (units + nw - 1) / nw;
+  int64_t u = row_a * L + gw * per;
+  const int64_t u_end = min(u + per, row_a * L + units);
   if (u >= u_end) return;
 
   // First token row of the span and its request.
