@@ -423,8 +423,8 @@ size_t lumen_kv_ckpt_marks_bytes(int64_t num_blocks);
  * the copies' (most negative code wins; read with lumen_kv_ckpt_status).
  * d_marks: caller-owned device scratch of marks_bytes >=
  * lumen_kv_ckpt_marks_bytes(num_blocks) bytes, 16-byte aligned, cleared by
- * this call (by a kernel, not a memset); it may be NULL only if num_blocks
- * is 0.  Calls sharing d_marks must not be in flight at the same time.
+ * the call where it needs it (by a kernel, not a memset; a small call keeps
+ * its bits on the chip); it may be NULL only if num_blocks is 0.  Calls sharing d_marks must not be in flight at the same time.
  * Nothing in the cache or the checkpoint is read or written. */
 int lumen_kv_ckpt_validate_targets(const lumen_kv_layout *layout,
                                    const int32_t *d_block_tables,

@@ -633,6 +633,35 @@ def test_validate_targets_matches_oracle(shape):
             assert got == want, (what, R, got, want)
 
 
+@pytest.mark.parametrize("R,cols,nb", [
+    (1, 16384, 131072), (1, 16385, 131072), (1, 9, 131073), (3, 1025, 131071),
+    (16, 1024, 131072), (16, 1025, 40000), (17, 70, 1190), (2, 3, 6)])
+def test_validate_either_side_of_its_small_path(R, cols, nb):
+    """Whole tables of the most requests, entries and blocks that one
+    workgroup validates, and of one more of each: clean, a block named twice
+    (by two requests, or a request's first and last page), an entry outside
+    the pool, the pool's last block, and a range past the table."""
+    shape = CacheShape(1, 1, 8, 4, NHD)
+    rng = np.random.default_rng(R * cols + nb)
+    bt = rng.permutation(nb)[:R * cols].reshape(R, cols).astype(np.int32)
+    if not (bt == nb - 1).any():
+        bt[R - 1, cols - 1] = nb - 1
+    s = np.zeros(R, np.int32)
+    e = np.full(R, cols * 4, np.int32)
+    s[R // 2] = 5  # the request's first page is not written
+    dup, bad, neg = bt.copy(), bt.copy(), bt.copy()
+    dup[R - 1, cols - 1] = dup[0, 1]
+    bad[R - 1, cols // 2] = nb
+    neg[0, cols - 1] = -1
+    past = e.copy()
+    past[R - 1] = cols * 4 + 1
+    for what, t, ee in (("clean", bt, e), ("dup", dup, e), ("bad", bad, e),
+                        ("negative", neg, e), ("past", bt, past),
+                        ("past and dup", dup, past)):
+        want = oracle.validate_targets(shape, nb, t, s, ee)
+        assert gpu_validate(shape, nb, t, s, ee) == want, what
+
+
 def test_validate_reuses_marks_and_strides_over_requests():
     """70000 one-page requests (more than one grid's worth of workgroups);
     the same marks buffer serves a call with a duplicate and then a clean
