@@ -1658,7 +1658,7 @@ def main():
         "per_request_mode": rounded(dec["per_request_mode"]),
         "other_path": rounded(dec["other_path"]),
         "roofline": {"bound": "hbm",
-                     "kernel": "copy_rows_kernel<%s, false, RangeWalk> (%s)"
+                     "kernel": "resident_copy_kernel<%s, false, true, false> (%s)"
                                % ("true" if dominant == "pack" else "false",
                                   dominant),
                      "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
