@@ -828,6 +828,18 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
   int32_t *first_tok = prefix + R + 1;
   const int32_t most = (int32_t(1) << 30) / R;  // tokens of one request
 
+  // Rows of the plan, -1 for the slow path.  A workspace that holds a plan of
+  // another number of requests has no rows, and its arrays may be shorter than
+  // this launch's: nothing of them is read.
+  auto plan_total = [&]() -> int32_t {
+    if (hdr->num_reqs != R) return 0;
+    const int64_t rows = hdr->total_rows;
+    return rows * g.row_pieces >= (int64_t(1) << 31) ||
+                   rows > (int64_t(1) << 30)
+               ? -1
+               : int32_t(rows);
+  };
+
   // Table t of the workgroup, by one wavefront.
   auto build = [&](int32_t t, int32_t total) {
     const int32_t row_a = int32_t(min(g.row_lo, int64_t(total)));
@@ -903,17 +915,13 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
         else if (blockIdx.x == 0 && __ballot(bad) != 0)
           record_error(err, LUMEN_ERR_RANGE);
       } else {
-        for (int32_t i = lane; i < R; i += kWave) {
-          prefix[i] = int32_t(ws_prefix[i]);
-          first_tok[i] = start[i];
-        }
-        const int64_t rows = hdr->total_rows;
-        total = hdr->num_reqs != R                           ? 0
-                : rows * g.row_pieces >= (int64_t(1) << 31) ||
-                          rows > (int64_t(1) << 30)
-                    ? -1
-                    : int32_t(rows);
-        if (hdr->num_reqs != R && blockIdx.x == 0)
+        total = plan_total();
+        if (hdr->num_reqs == R)
+          for (int32_t i = lane; i < R; i += kWave) {
+            prefix[i] = int32_t(ws_prefix[i]);
+            first_tok[i] = start[i];
+          }
+        else if (blockIdx.x == 0)
           record_error(err, LUMEN_ERR_INVALID_ARG);
       }
       if (lane == 0) sh_total = total;
@@ -937,17 +945,13 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
       if (big || int64_t(total) * g.row_pieces >= (int64_t(1) << 31))
         total = -1;
     } else {
-      for (int32_t i = tid; i < R; i += kBlockThreads) {
-        prefix[i] = int32_t(ws_prefix[i]);
-        first_tok[i] = start[i];
-      }
-      const int64_t rows = hdr->total_rows;
-      total = hdr->num_reqs != R                           ? 0
-              : rows * g.row_pieces >= (int64_t(1) << 31) ||
-                        rows > (int64_t(1) << 30)
-                  ? -1
-                  : int32_t(rows);
-      if (hdr->num_reqs != R && blockIdx.x == 0 && wave == 0)
+      total = plan_total();
+      if (hdr->num_reqs == R)
+        for (int32_t i = tid; i < R; i += kBlockThreads) {
+          prefix[i] = int32_t(ws_prefix[i]);
+          first_tok[i] = start[i];
+        }
+      else if (blockIdx.x == 0 && wave == 0)
         record_error(err, LUMEN_ERR_INVALID_ARG);
       __syncthreads();
     }
@@ -1088,6 +1092,9 @@ __global__ __launch_bounds__(kPlanThreads) void item_scan_kernel(
     int32_t block_size) {
   constexpr int kWaves = kPlanThreads / kWave;
   __shared__ int64_t wave_sum[kWaves];
+  // A plan of another number of requests: its arrays may be shorter than R
+  // (the pack after this one finds the same and records it).
+  if (hdr->num_reqs != R) return;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wid = tid / kWave;

@@ -180,3 +180,41 @@ def test_page_major_walk_at_small_sizes():
                          capture_output=True, text=True, timeout=110)
     assert out.returncode == 0 and "forced walks ok" in out.stdout, \
         out.stdout[-2000:] + out.stderr[-2000:]
+
+
+WRONG_PLAN = {
+    # what copies over a plan of another number of requests, and into how
+    # many bytes of checkpoint
+    "resident, one wavefront": (CacheShape(3, 4, 64, 4, NHD), 200, 0),
+    "resident, a workgroup": (CacheShape(3, 4, 64, 4, HND), 1500, 0),
+    "page-major": (CacheShape(16, 1, 128, 16, NHD), 300, 128 << 20),
+    "span": (CacheShape(3, 4, 64, 4, NHD), 4097, 0),
+}
+
+
+@pytest.mark.parametrize("name", list(WRONG_PLAN))
+def test_plan_of_fewer_requests_is_refused_untouched(name):
+    """Copies of R requests over a workspace that holds a plan of two: they
+    record INVALID_ARG, copy nothing, and leave everything behind that plan's
+    bytes of the workspace alone (a caller that sized the workspace for two
+    requests has other data there, or nothing).  The tensor is R requests
+    long underneath."""
+    shape, R, ckpt_bytes = WRONG_PLAN[name]
+    nb = 8
+    rng = np.random.default_rng(R)
+    bt = h2d(rng.integers(0, nb, (R, 2)).astype(np.int32))
+    rows = max(R, ckpt_bytes // shape.token_row_bytes)
+    pool = h2d(W.random_words(rng, shape.pool_elems(nb), shape.elem_bytes))
+    was = pool.clone()
+    ck = torch.full((rows * shape.token_row_elems,), 0x5A, dtype=pool.dtype,
+                    device=dev())
+    two = kv.lumen_kv_ckpt_plan_workspace_bytes(2)
+    ws = kv.new_workspace(R, dev())
+    s, e = h2d(np.zeros(2, np.int32)), h2d(np.ones(2, np.int32))
+    for copy in (kv.lumen_kv_ckpt_pack, kv.lumen_kv_ckpt_unpack):
+        ws[two:] = 0x5A
+        kv.lumen_kv_ckpt_plan(s, e, ws)
+        copy(shape, nb, pool, bt, ws, ck)
+        assert kv.lumen_kv_ckpt_status(ws) == kv.LUMEN_ERR_INVALID_ARG
+        assert (ws[two:] == 0x5A).all()
+        assert (ck == 0x5A).all() and torch.equal(pool, was)
