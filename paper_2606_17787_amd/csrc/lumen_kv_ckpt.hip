@@ -514,6 +514,16 @@ __device__ __forceinline__ bool range_ok(int32_t s, int32_t e) {
   return s >= 0 && e >= s;
 }
 
+// Orders the wavefront's LDS accesses across its lanes: what a lane wrote
+// before it, any lane reads after it.  LDS operations of a wavefront execute
+// in order, so this costs no instruction; it keeps the compiler from moving a
+// read over another lane's write.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Dynamic LDS of the copy kernels that keep a row or page prefix there.
 extern __shared__ __align__(16) int64_t copy_lds[];
 
@@ -925,6 +935,7 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
           record_error(err, LUMEN_ERR_INVALID_ARG);
       }
       if (lane == 0) sh_total = total;
+      wave_lds_fence();  // build reads prefixes that other lanes wrote
       if (total > 0) build(0, total);
     } else {
       // three wavefronts, four groups of lanes
