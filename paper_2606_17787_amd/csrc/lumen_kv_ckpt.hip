@@ -493,23 +493,6 @@ __device__ __forceinline__ int64_t wave_inclusive_sum(int64_t x) {
   return x;
 }
 
-// The same in 32 bits.
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ int32_t add_dpp(int32_t x) {
-  return x + __builtin_amdgcn_update_dpp(0, x, kCtrl, kRowMask, 0xf, true);
-}
-
-__device__ __forceinline__ int32_t wave_inclusive_sum(int32_t x) {
-  constexpr int kRowShr = 0x110, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-  x = add_dpp<kRowShr + 1, 0xf>(x);
-  x = add_dpp<kRowShr + 2, 0xf>(x);
-  x = add_dpp<kRowShr + 4, 0xf>(x);
-  x = add_dpp<kRowShr + 8, 0xf>(x);
-  x = add_dpp<kRowBcast15, 0xa>(x);
-  x = add_dpp<kRowBcast31, 0xc>(x);
-  return x;
-}
-
 __device__ __forceinline__ bool range_ok(int32_t s, int32_t e) {
   return s >= 0 && e >= s;
 }
@@ -631,50 +614,49 @@ __global__ __launch_bounds__(kBlockThreads) LUMEN_COPY_OCCUPANCY void copy_rows_
 // LDS); a wavefront scan and the wavefronts' totals give each chunk its
 // start; each thread then turns its counts into prefixes in place.  An
 // invalid range counts no tokens and is reported once per launch (RANGE), by
-// workgroup 0.  Returns whether a request has more than `most` tokens (the
-// sums may then not fit T).
+// workgroup 0.  The sums are in 64 bits; the prefix holds them as T, where
+// the total fits it.  Returns the total.
 template <class T>
-__device__ __forceinline__ bool scan_ranges(const int32_t *start,
-                                            const int32_t *end, int32_t R,
-                                            T *prefix, int32_t *first_tok,
-                                            T *wave_tot, int32_t most,
-                                            int32_t *err, T &total) {
+__device__ __forceinline__ int64_t scan_ranges(const int32_t *start,
+                                               const int32_t *end, int32_t R,
+                                               T *prefix, int32_t *first_tok,
+                                               int64_t *wave_tot,
+                                               int32_t *err) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int32_t per = (R + kBlockThreads - 1) / kBlockThreads;
   const int32_t lo = min(R, tid * per), hi = min(R, lo + per);
-  T local = 0;
-  int flags = 0;  // bit 0: an invalid range, bit 1: a long one
+  int64_t local = 0;
+  int bad = 0;
 #pragma unroll 4
   for (int32_t i = lo; i < hi; ++i) {
     const int32_t s = start[i], e = end[i];
     const bool ok = range_ok(s, e);
     const int32_t n = ok ? e - s : 0;
-    flags |= (ok ? 0 : 1) | (n > most ? 2 : 0);
+    bad |= !ok;
     prefix[i] = n;
     if (first_tok) first_tok[i] = s;
     local += n;
   }
-  const T incl = wave_inclusive_sum(local);
+  const int64_t incl = wave_inclusive_sum(local);
   if (lane == kWave - 1) wave_tot[wave] = incl;
   __syncthreads();
-  T base = 0;
-  total = 0;
+  int64_t base = 0, total = 0;
 #pragma unroll
   for (int w = 0; w < kWavesPerBlock; ++w) {
-    const T x = wave_tot[w];
+    const int64_t x = wave_tot[w];
     if (w < wave) base += x;
     total += x;
   }
-  T run = base + incl - local;
+  T run = T(base + incl - local);
   for (int32_t i = lo; i < hi; ++i) {
     const T n = prefix[i];
     prefix[i] = run;
     run += n;
   }
-  if (tid == 0) prefix[R] = total;
-  const bool bad = __syncthreads_or(flags & 1), big = __syncthreads_or(flags & 2);
-  if (bad && blockIdx.x == 0 && wave == 0) record_error(err, LUMEN_ERR_RANGE);
-  return big;
+  if (tid == 0) prefix[R] = T(total);
+  if (__syncthreads_or(bad) && blockIdx.x == 0 && wave == 0)
+    record_error(err, LUMEN_ERR_RANGE);
+  return total;
 }
 
 // The last index r in [0, n) with pre[r] <= x, one search per lane
@@ -796,10 +778,10 @@ __device__ __forceinline__ void store_piece(const uint4 (&buf)[kUnroll],
 // offsets: the chain of dependent loads is paid once per 64 pieces, where
 // the span walk pays it per wavefront.  The builder changes from workgroup
 // to workgroup on a CU, to spread it over the SIMDs; later tables are built
-// while the one before is copied.  Everything is in 32 bits; what does not
-// fit (a request of more than 2^30 / num_reqs tokens, or 2^31 pieces: nearly
-// all of their rows are necessarily invalid) takes the slow path, which
-// walks whole rows, one per lane, in 64 bits.
+// while the one before is copied.  Prefixes and piece numbers are in 32 bits;
+// more rows than 2^30 or pieces than 2^31 in all (terabytes of checkpoint, but
+// for rows of a few hundred bytes: such ranges lie past their block tables)
+// take the slow path, which walks whole rows, one per lane, in 64 bits.
 //
 // What bounds it: small steps the set-up (about 3 us from the start of the
 // kernel to the first copy) and the launch; large ones HBM.  Kernels that
@@ -836,18 +818,20 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
   int64_t *wave_tot = copy_lds;  // [kWavesPerBlock]
   int32_t *prefix = reinterpret_cast<int32_t *>(copy_lds + kWavesPerBlock);
   int32_t *first_tok = prefix + R + 1;
-  const int32_t most = (int32_t(1) << 30) / R;  // tokens of one request
 
-  // Rows of the plan, -1 for the slow path.  A workspace that holds a plan of
-  // another number of requests has no rows, and its arrays may be shorter than
-  // this launch's: nothing of them is read.
-  auto plan_total = [&]() -> int32_t {
-    if (hdr->num_reqs != R) return 0;
-    const int64_t rows = hdr->total_rows;
-    return rows * g.row_pieces >= (int64_t(1) << 31) ||
-                   rows > (int64_t(1) << 30)
+  // The launch's rows in 32 bits, or -1: the slow path.  Decided on the true
+  // total: one long request among many short ones fits.
+  auto narrow = [&](int64_t rows) -> int32_t {
+    return rows > (int64_t(1) << 30) ||
+                   rows * g.row_pieces >= (int64_t(1) << 31)
                ? -1
                : int32_t(rows);
+  };
+  // Rows of the plan.  A workspace that holds a plan of another number of
+  // requests has none, and its arrays may be shorter than this launch's:
+  // nothing of them is read.
+  auto plan_total = [&]() -> int32_t {
+    return hdr->num_reqs == R ? narrow(hdr->total_rows) : 0;
   };
 
   // Table t of the workgroup, by one wavefront.
@@ -887,10 +871,10 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
   if (few) {
     if (wave == builder) {
       constexpr int kPer = kFewReqs / kWave;
-      int32_t n[kPer], local = 0;
       if (kRanges) {
-        int32_t s[kPer], e[kPer];
-        bool bad = false, big = false;
+        int32_t s[kPer], e[kPer], n[kPer];
+        int64_t local = 0;
+        bool bad = false;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           const int32_t i = lane * kPer + j;
@@ -902,11 +886,10 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
           const bool ok = range_ok(s[j], e[j]);
           n[j] = ok ? e[j] - s[j] : 0;
           bad |= !ok;
-          big |= n[j] > most;
           local += n[j];
         }
-        const int32_t incl = wave_inclusive_sum(local);
-        int32_t run = incl - local;
+        const int64_t incl = wave_inclusive_sum(local);
+        int32_t run = int32_t(incl - local);
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           const int32_t i = lane * kPer + j;
@@ -916,13 +899,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
           }
           run += n[j];
         }
-        total = __builtin_amdgcn_readlane(incl, kWave - 1);
-        const bool slow =
-            __ballot(big) != 0 ||
-            int64_t(total) * g.row_pieces >= (int64_t(1) << 31);
-        if (slow)
-          total = -1;
-        else if (blockIdx.x == 0 && __ballot(bad) != 0)
+        total = narrow(readlane64(incl, kWave - 1));
+        if (blockIdx.x == 0 && __ballot(bad) != 0)
           record_error(err, LUMEN_ERR_RANGE);
       } else {
         total = plan_total();
@@ -949,12 +927,8 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
     total = __builtin_amdgcn_readfirstlane(sh_total);
   } else {
     if (kRanges) {
-      const bool big = scan_ranges<int32_t>(
-          start, end, R, prefix, first_tok,
-          reinterpret_cast<int32_t *>(wave_tot), most, err, total);
-      total = __builtin_amdgcn_readfirstlane(total);
-      if (big || int64_t(total) * g.row_pieces >= (int64_t(1) << 31))
-        total = -1;
+      total = __builtin_amdgcn_readfirstlane(narrow(scan_ranges(
+          start, end, R, prefix, first_tok, wave_tot, err)));
     } else {
       total = plan_total();
       if (hdr->num_reqs == R)
@@ -1041,8 +1015,7 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
   int64_t rows64;
   if (kRanges) {
     __syncthreads();  // the 32-bit prefix is no longer read
-    scan_ranges<int64_t>(start, end, R, prefix64, nullptr, wave_tot, INT32_MAX,
-                         err, rows64);
+    rows64 = scan_ranges(start, end, R, prefix64, nullptr, wave_tot, err);
   } else {
     rows64 = hdr->total_rows;
   }

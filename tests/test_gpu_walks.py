@@ -106,17 +106,45 @@ def test_resident_walk_fills_its_table_again(name, via):
     assert torch.equal(d, h2d(src))
 
 
+@pytest.mark.parametrize("via", ["plan", "ranges"])
+@pytest.mark.parametrize("R", [1024, 4096])
+def test_one_long_request_among_many(R, via):
+    """A context of a million tokens among requests of one, and one of 300
+    thousand among 4,096: what decides between 32 and 64 bits is the sum of
+    the rows, not the longest request's."""
+    shape = CacheShape(1, 1, 16, 128, NHD, 1)
+    n = np.ones(R, np.int64)
+    n[R // 3] = (1 << 30) // R + 38000
+    s = np.zeros(R, np.int32)
+    s[R // 2:] = 3
+    rng = np.random.default_rng(R)
+    used = -(-(s + n) // shape.block_size)
+    nb = int(used.sum())
+    bt = np.full((R, int(used.max())), -1, np.int32)
+    bt2 = bt.copy()
+    p, p2, k = rng.permutation(nb), rng.permutation(nb), 0
+    for r in range(R):
+        bt[r, :used[r]] = p[k:k + used[r]]
+        bt2[r, :used[r]] = p2[k:k + used[r]]
+        k += used[r]
+    src = W.random_words(rng, shape.pool_elems(nb), 1)
+    dst = W.random_words(rng, shape.pool_elems(nb), 1)
+    e = (s + n).astype(np.int32)
+    ref = oracle_path(shape, nb, src, bt, s, e, nb, dst.copy(), bt2)
+    got = gpu_path(shape, nb, src, bt, s, e, nb, dst, bt2, via=via)
+    assert_same(got, ref, f"R={R} {via}")
+
+
 @pytest.mark.parametrize("R", [2, 256, 300, 4096])
 def test_slow_path_copies_the_valid_rows(R):
-    """A request of more tokens than the 32-bit path takes (2^30 / R), of
-    which only the first lie in its block table: the valid rows of every
-    request are copied, the others are RANGE errors."""
+    """More rows than the 32-bit path takes (2^30 in all), of which only the
+    first lie in their block table: the valid rows of every request are
+    copied, the others are RANGE errors."""
     shape = CacheShape(2, 2, 16, 4, NHD)
     bs, cols = shape.block_size, 2
     s = np.zeros(R, np.int32)
     e = np.full(R, 1, np.int32)
-    long = min(2**31 - 1, (1 << 30) // R + 1)
-    e[R // 2] = long
+    e[R // 2] = (1 << 30) + 1
     rng = np.random.default_rng(R)
     nb = 2 * R
     bt = rng.permutation(nb).astype(np.int32).reshape(R, cols)
