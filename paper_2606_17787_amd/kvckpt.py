@@ -150,9 +150,14 @@ def layout(shape, num_blocks: int) -> lumen_kv_layout:
 # library: the marshalling below is kept well under that.  Pointers and stream
 # handles are passed as integers (the argument types convert them), and the
 # current device is read without torch.cuda.current_device's initialisation
-# check, which a tensor on a device has been through.
-_current_device = torch._C._cuda_getDevice
-_current_raw_stream = torch._C._cuda_getCurrentRawStream
+# check, which a tensor on a device has been through.  (A torch built without
+# a GPU has neither function; the host libraries of this package, which import
+# this module, need none.)
+_current_device = getattr(torch._C, "_cuda_getDevice",
+                          torch.cuda.current_device)
+_current_raw_stream = getattr(
+    torch._C, "_cuda_getCurrentRawStream",
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:

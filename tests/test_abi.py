@@ -2,6 +2,7 @@
 header declares, and rejects bad host-side arguments before any HIP call
 (the fake pointers below are never dereferenced)."""
 import ctypes
+import os
 
 import pytest
 
@@ -399,3 +400,25 @@ def test_headers_compile_on_their_own(header, lang):
                         "-I", inc, os.path.join(inc, header)],
                        capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stderr
+
+
+def test_modules_import_under_a_torch_without_a_gpu():
+    """The host libraries' bindings (and the package's own) import where
+    torch has no device functions, and device calls then raise torch's own
+    error."""
+    import subprocess
+    import sys
+    code = (
+        "import torch\n"
+        "for n in ('_cuda_getDevice', '_cuda_getCurrentRawStream'):\n"
+        "    delattr(torch._C, n)\n"
+        "from paper_2606_17787_amd import tags, sched, progress, kvckpt as kv\n"
+        "assert tags.exported_names() and sched.exported_names()\n"
+        "try:\n"
+        "    kv._stream_handle(None)\n"
+        "except (RuntimeError, AssertionError):\n"
+        "    print('imported')\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True,
+                       text=True, cwd=os.path.dirname(kv.PKG),
+                       env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"))
+    assert r.returncode == 0 and r.stdout.strip() == "imported", r.stderr
