@@ -795,7 +795,6 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
     const void *__restrict__ p1, const void *__restrict__ p2,
     const void *__restrict__ p3, int64_t row_base, int32_t *err, Geom g) {
   constexpr int kRounds = kWave / kWavesPerBlock;  // rounds per table
-  static_assert(kBlockThreads == kPieceVecs, "one lane offset per thread");
   __shared__ int64_t tab_cache[2][kWave], tab_ckpt[2][kWave];
   __shared__ int32_t tab_nvec[2][kWave], tab_v0[2][kWave];
   __shared__ int64_t offs[kPieceVecs];
@@ -805,7 +804,7 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
   const bool few = R <= kFewReqs;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int builder = (blockIdx.x / g.cus) & (kWavesPerBlock - 1);
+  const int builder = (blockIdx.x / g.cus) % kWavesPerBlock;
 
   // Ranges: starts, ends, per-request row bases (or null).  Plan: header,
   // row prefix, each request's first row, starts.
@@ -915,13 +914,14 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
       if (lane == 0) sh_total = total;
       wave_lds_fence();  // build reads prefixes that other lanes wrote
       if (total > 0) build(0, total);
-    } else {
-      // three wavefronts, four groups of lanes
-      for (int k = (wave - builder - 1) & (kWavesPerBlock - 1);
-           k < kWavesPerBlock; k += kWavesPerBlock - 1)
-        if (!kSplit)
-          offs[k * kWave + lane] =
-              cache_vec_offset<kHeadMajor>(k * kWave + lane, g);
+    }
+    if (!kSplit && (wave != builder || kWavesPerBlock == 1)) {
+      // the offsets, by the other wavefronts
+      constexpr int kOthers = kWavesPerBlock > 1 ? kWavesPerBlock - 1 : 1;
+      for (int k = (wave - builder - 1 + kWavesPerBlock) % kWavesPerBlock;
+           k < kUnroll; k += kOthers)
+        offs[k * kWave + lane] =
+            cache_vec_offset<kHeadMajor>(k * kWave + lane, g);
     }
     __syncthreads();
     total = __builtin_amdgcn_readfirstlane(sh_total);
@@ -940,7 +940,9 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
         record_error(err, LUMEN_ERR_INVALID_ARG);
       __syncthreads();
     }
-    if (!kSplit) offs[tid] = cache_vec_offset<kHeadMajor>(tid, g);
+    if (!kSplit)
+      for (int k = tid; k < kPieceVecs; k += kBlockThreads)
+        offs[k] = cache_vec_offset<kHeadMajor>(k, g);
     if (wave == builder && total > 0) build(0, total);
     __syncthreads();
   }

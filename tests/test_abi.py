@@ -422,3 +422,20 @@ def test_modules_import_under_a_torch_without_a_gpu():
                        text=True, cwd=os.path.dirname(kv.PKG),
                        env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"))
     assert r.returncode == 0 and r.stdout.strip() == "imported", r.stderr
+
+
+@pytest.mark.parametrize("threads,unroll", [(64, 4), (192, 2), (512, 8)])
+def test_kernels_compile_with_other_launch_shapes(threads, unroll):
+    """The kernels' compile-time knobs take other values than their defaults
+    (threads per workgroup, vectors in flight per lane)."""
+    import subprocess
+    from paper_2606_17787_amd import build
+    cmd = [os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin",
+                        "hipcc"),
+           *[f for f in build.HIPCC_FLAGS if f not in ("-fPIC", "-shared")],
+           "-Wno-unused-command-line-argument",
+           f"-DLUMEN_KV_CKPT_BLOCK_THREADS={threads}",
+           f"-DLUMEN_KV_CKPT_UNROLL={unroll}", "-I", build.INCLUDE,
+           "--offload-device-only", "-fsyntax-only", build.SRC]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
