@@ -1580,18 +1580,19 @@ __global__ __launch_bounds__(kSmallThreads) void validate_small_kernel(
   if (tid == 0 && worst != LUMEN_OK) atomicMin(err, worst);
 }
 
-// Draft-state alignment, step 1: one workgroup per request (grid-strided)
-// finds the first position where the draft and committed tokens differ, 4096
-// positions per round (1024 per wavefront, 16 per lane, all loads in flight
-// together), truncates the request's KV length to it, and counts the
+// Draft-state alignment, step 1: a workgroup (kWide) or a wavefront per request
+// (grid-strided) finds the first position where the draft and committed tokens
+// differ, 1024 positions per wavefront and round (16 per lane, all loads in
+// flight together), truncates the request's KV length to it, and counts the
 // allocated table entries of the pages the shorter KV no longer reaches.  Per
 // request it leaves in the workspace the count (-1 for a request with
 // inconsistent lengths, which is left unchanged) and the page span [lo, hi)
-// packed into one int64.  A histories' compare is bound by latency, not by
-// its bytes: a wavefront per request took a round trip per 1024 tokens of the
-// longest history.
+// packed into one int64.  The compare is bound by latency, not by its bytes:
+// a wavefront takes a round trip per 1024 tokens of its request's history,
+// and a workgroup's other wavefronts have nothing to read in a short one.
 constexpr int kMatch = 16;  // positions per lane and round
 
+template <bool kWide>
 __global__ __launch_bounds__(kBlockThreads) void draft_match_kernel(
     const int32_t *__restrict__ draft, int32_t draft_cols,
     const int32_t *__restrict__ draft_len,
@@ -1600,34 +1601,41 @@ __global__ __launch_bounds__(kBlockThreads) void draft_match_kernel(
     const int32_t *__restrict__ block_tables, int32_t bt_cols,
     int32_t block_size, int32_t num_reqs, int32_t *replay, int64_t *count,
     int64_t *span) {
-  __shared__ int32_t first_diff[2];  // by round, alternately
+  __shared__ int32_t first_diff[2];  // kWide: by round, alternately
   __shared__ int32_t entries;
+  constexpr int kThreads = kWide ? kBlockThreads : kWave;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  for (int64_t r = blockIdx.x; r < num_reqs; r += gridDim.x) {
+  const int me = kWide ? tid : lane;
+  const int64_t groups = int64_t(gridDim.x) * (kWide ? 1 : kWavesPerBlock);
+  for (int64_t r = kWide ? int64_t(blockIdx.x)
+                         : int64_t(blockIdx.x) * kWavesPerBlock + wave;
+       r < num_reqs; r += groups) {
     const int32_t dl = draft_len[r], cl = committed_len[r], kl = kv_len[r];
     if (dl < 0 || cl < 0 || kl < 0 || dl > draft_cols ||
         cl > committed_cols || int64_t(kl) > int64_t(bt_cols) * block_size) {
-      if (tid == 0) {
+      if (me == 0) {
         count[r] = -1;
         span[r] = 0;
         replay[r] = 0;
       }
       continue;
     }
-    if (tid == 0) {
-      first_diff[0] = INT32_MAX;
-      entries = 0;
+    if (kWide) {
+      if (tid == 0) {
+        first_diff[0] = INT32_MAX;
+        entries = 0;
+      }
+      __syncthreads();
     }
-    __syncthreads();
     const int32_t lim = min(dl, cl);
     const int32_t *d = draft + r * draft_cols;
     const int32_t *c = committed + r * committed_cols;
     int32_t p = lim;
     // (64-bit: a round's end may pass INT32_MAX)
     int64_t base = 0;
-    for (int round = 0; base < lim; base += kBlockThreads * kMatch, ++round) {
-      const int64_t at = base + wave * (kWave * kMatch) + lane;
+    for (int round = 0; base < lim; base += kThreads * kMatch, ++round) {
+      const int64_t at = base + (kWide ? wave * (kWave * kMatch) : 0) + lane;
       int32_t dv[kMatch], cv[kMatch];
 #pragma unroll
       for (int k = 0; k < kMatch; ++k) {
@@ -1639,15 +1647,25 @@ __global__ __launch_bounds__(kBlockThreads) void draft_match_kernel(
 #pragma unroll
       for (int k = kMatch - 1; k >= 0; --k)
         if (dv[k] != cv[k]) mine = int32_t(at + k * kWave);
-      if (mine != INT32_MAX) atomicMin(&first_diff[round & 1], mine);
-      __syncthreads();
-      const int32_t found = first_diff[round & 1];
-      if (found != INT32_MAX) {  // the same for every thread
+      int32_t found;  // the same for every thread of the group
+      if (kWide) {
+        if (mine != INT32_MAX) atomicMin(&first_diff[round & 1], mine);
+        __syncthreads();
+        found = first_diff[round & 1];
+      } else {
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1)
+          mine = min(mine, __shfl_xor(mine, off, kWave));
+        found = mine;
+      }
+      if (found != INT32_MAX) {
         p = found;
         break;
       }
-      if (tid == 0) first_diff[(round + 1) & 1] = INT32_MAX;
-      __syncthreads();
+      if (kWide) {
+        if (tid == 0) first_diff[(round + 1) & 1] = INT32_MAX;
+        __syncthreads();
+      }
     }
     const int32_t valid = min(kl, p);
     const int32_t lo = int32_t((int64_t(valid) + block_size - 1) / block_size);
@@ -1655,9 +1673,10 @@ __global__ __launch_bounds__(kBlockThreads) void draft_match_kernel(
     const int32_t *row = block_tables + r * bt_cols;
     // (few pages at most: counted by one wavefront where they fit it)
     int64_t n = 0;
-    if (hi - lo <= kWave) {
-      if (wave == 0)
-        n = __popcll(__ballot(lo + lane < hi && row[lo + lane] >= 0));
+    if (!kWide || hi - lo <= kWave) {
+      if (!kWide || wave == 0)
+        for (int32_t j = lo; j < hi; j += kWave)
+          n += __popcll(__ballot(j + lane < hi && row[j + lane] >= 0));
     } else {
       int32_t mine = 0;
       for (int32_t j = lo + tid; j < hi; j += kBlockThreads)
@@ -1666,13 +1685,13 @@ __global__ __launch_bounds__(kBlockThreads) void draft_match_kernel(
       __syncthreads();
       n = entries;
     }
-    if (tid == 0) {
+    if (me == 0) {
       kv_len[r] = valid;
       replay[r] = cl - valid;
       count[r] = n;
       span[r] = (int64_t(lo) << 32) | int64_t(hi);
     }
-    __syncthreads();  // the next request's first_diff and entries
+    if (kWide) __syncthreads();  // the next request's first_diff and entries
   }
 }
 
@@ -2719,10 +2738,25 @@ int lumen_kv_draft_align(const int32_t *d_draft, int32_t draft_cols,
   hipStream_t s = static_cast<hipStream_t>(stream);
   clear_pending_error();
   if (num_reqs > 0) {
-    int64_t blocks = num_reqs;
-    const int64_t cap = int64_t(dev->cus) * 32;
+    // A workgroup per request while that many fit the chip at once, or where
+    // histories may take a wavefront many rounds.  us a call in a graph, by
+    // wavefront against by workgroup, histories as long as the columns (the
+    // shorter of the two arrays): 1024 columns, 512 requests 7.5 / 7.3, 1024
+    // 8.1 / 8.5, 4096 10.7 / 15.2; 2048 columns, 1024 requests 9.0 / 8.5, 2048
+    // 10.4 / 10.9; 4096 columns, 1024 requests 13.4 / 9.3, 16384 113 / 111; of
+    // 700 tokens (median) in 4096 columns, 2048 requests 10.2 / 10.5.
+    const int32_t cols = draft_cols < committed_cols ? draft_cols : committed_cols;
+    const int64_t rounds = int64_t(cols) / (kWave * kMatch) +
+                           (cols % (kWave * kMatch) != 0);
+    const bool wide = rounds > 2 || num_reqs <= 2 * int64_t(dev->cus) * rounds;
+    int64_t blocks =
+        wide ? num_reqs
+             : (int64_t(num_reqs) + kWavesPerBlock - 1) / kWavesPerBlock;
+    const int64_t cap = int64_t(dev->cus) * (wide ? 32 : 8);
     if (blocks > cap) blocks = cap;
-    hipLaunchKernelGGL(draft_match_kernel, dim3(unsigned(blocks)),
+    hipLaunchKernelGGL(wide ? &draft_match_kernel<true>
+                            : &draft_match_kernel<false>,
+                       dim3(unsigned(blocks)),
                        dim3(kBlockThreads), 0, s, d_draft, draft_cols,
                        d_draft_len, d_committed, committed_cols,
                        d_committed_len, d_kv_len, d_block_tables, bt_cols,

@@ -65,6 +65,80 @@ def test_draft_align_matches_oracle(R, bs):
         assert np.array_equal(tab, tab_o)
 
 
+def check(draft, dl, committed, cl, kl, bt, bs, cap=10**7):
+    want = D.align(draft, dl, committed, cl, kl, bt, bs, cap)
+    st, k, rp, fr, tab, tot = run_gpu(draft, dl, committed, cl, kl, bt, bs,
+                                      min(cap, bt.size))
+    assert st == want[0]
+    for got, w in ((k, want[1]), (rp, want[2]), (tab, want[4])):
+        assert np.array_equal(got, w)
+    n = len(want[3])
+    assert np.array_equal(fr[:n], want[3]) and (fr[n:] == -9).all()
+    assert tot == want[5]
+
+
+# A wavefront compares 1,024 positions a round, and a workgroup of four, one
+# per request while the requests are few or their histories long, 4,096.
+@pytest.mark.parametrize("cols", [1023, 1024, 1025, 2048, 2049, 4095, 4096,
+                                  4097, 8193, 9000])
+def test_draft_align_long_histories(cols):
+    """A mismatch at either edge of every wavefront's slice of every round, at
+    random positions, at the last position and nowhere; a second mismatch
+    after it; histories that end before it."""
+    rng = np.random.default_rng(cols)
+    at = [p for k in range(0, cols, 1024) for p in (k, k + 1, k + 1023)
+          if p < cols] + [cols - 1, None]
+    at += list(rng.integers(0, cols, 6)) + [None, 5]
+    R, bs = len(at), 16
+    draft = rng.integers(0, 50000, (R, cols)).astype(np.int32)
+    committed = draft.copy()
+    for r, p in enumerate(at):
+        if p is not None:
+            committed[r, p] += 1
+            committed[r, min(cols - 1, p + 1 + r % 1500)] += 1
+    full = np.full(R, cols, np.int32)
+    dl, cl, kl = full.copy(), full.copy(), full.copy()
+    cl[-2], dl[-1] = cols - 1, 5  # ends before the mismatch, and at it
+    kl[3] = 2
+    pages = -(-cols // bs) + 1
+    bt = rng.permutation(R * pages).reshape(R, pages).astype(np.int32)
+    bt[rng.random(bt.shape) < 0.05] = -1
+    check(draft, dl, committed, cl, kl, bt, bs)
+    check(draft, dl, committed, cl, kl, bt, bs, cap=7)
+
+
+def test_draft_align_two_rounds_by_wavefront():
+    """More requests than take a workgroup each at two rounds of columns."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    R, cols, bs = 4 * cus + 9, 1100, 32
+    rng = np.random.default_rng(4)
+    draft = rng.integers(0, 50000, (R, cols)).astype(np.int32)
+    committed = draft.copy()
+    r = np.arange(R)
+    committed[r, rng.integers(0, cols, R)] += r % 3 != 0
+    kl = rng.integers(cols - 300, cols + 1, R).astype(np.int32)
+    full = np.full(R, cols, np.int32)
+    pages = -(-cols // bs)
+    bt = rng.permutation(R * pages).reshape(R, pages).astype(np.int32)
+    check(draft, full, committed, full, kl, bt, bs)
+
+
+@pytest.mark.parametrize("cols", [40, 2049])
+def test_draft_align_more_requests_than_the_grid(cols):
+    """The grid strides over the requests (by wavefront and, at three rounds
+    of columns, by workgroup), with inconsistent lengths between them."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    R, bs = 2 * 32 * cus + 37, 4
+    rng = np.random.default_rng(cols)
+    draft, dl, committed, cl, kl, bt = case(rng, R, 40, bs)
+    bad = rng.random(R) < 0.1
+    dl[bad & (dl % 2 == 0)] = cols + 1
+    cl[bad & (dl % 2 == 1)] = -1
+    wide = [np.zeros((R, cols), np.int32) for _ in range(2)]
+    wide[0][:, :40], wide[1][:, :40] = draft, committed
+    check(wide[0], dl, wide[1], cl, kl, bt, bs)
+
+
 def test_draft_align_range_errors_and_empty():
     rng = np.random.default_rng(2)
     draft, dl, committed, cl, kl, bt = case(rng, 6, 30, 4)
