@@ -119,8 +119,11 @@ constexpr int kUnroll = LUMEN_KV_CKPT_UNROLL;
 constexpr int kDefaultWavesPerCU = LUMEN_KV_CKPT_WAVES_PER_CU;
 constexpr int64_t kMinWaveBytes = LUMEN_KV_CKPT_MIN_WAVE_BYTES;
 constexpr int32_t kPieceVecs = kWave * kUnroll;  // resident walk: 4 KiB
-// Requests up to which every wavefront of the resident walk scans the ranges
-// by itself (four per lane).
+// Requests up to which one wavefront of each resident workgroup scans the
+// ranges (four per lane) and builds the first table with no barrier between;
+// above, the workgroup scans them.  us for a pack and an unpack of one token
+// per request (40 KiB rows) with 128 / 256 / 512 here: 64 requests 9.9 / 10.3
+// / 11.3, 200 15.6 / 15.3 / 16.2, 300 17.3 / 17.5 / 18.6.
 constexpr int32_t kFewReqs = 4 * kWave;
 constexpr int64_t kMinWavesPerCU = LUMEN_KV_CKPT_MIN_WAVES_PER_CU;
 
@@ -761,7 +764,7 @@ __device__ __forceinline__ void store_piece(const uint4 (&buf)[kUnroll],
 // holds, not how many the ranges name, so a grid sized by the buffer is
 // mostly idle workgroups when a few requests append to a large arena, each
 // of which still pays its set-up.  Here the grid is what the chip can hold
-// (kResidentBlocks workgroups per CU) and the workgroups stride over the
+// (up to kResidentBlocks workgroups per CU) and the workgroups stride over the
 // pieces that exist.
 //
 // A piece is at most kPieceVecs vectors (4 KiB) of one token row: whole
@@ -1796,6 +1799,15 @@ static_assert(sizeof(int64_t) * (kRangesMaxReqs + 1 + kWavesPerBlock) <=
 // per SIMD.  6, 12, 16 and 24 per CU were within 1% on decode steps that
 // fill the chip (217-220 us) and 24 cost small steps 2 us.
 constexpr int64_t kResidentBlocks = 32 / kWavesPerBlock;
+// Or fewer, what its LDS holds: with the prefixes of 4,096 requests a CU holds
+// 4 workgroups of the default size, and a grid of 8 sets up twice.  Small
+// rows (1 KiB), 1-8 a request, us for a pack and an unpack over the ranges, 8
+// per CU against what fits: 2,048 requests 30.7 / 26.1, 4,096 75.1 / 48.7.
+constexpr int64_t kCuLds = int64_t(160) << 10;
+// Bound of the resident walk's static LDS (tables, lane offsets).
+constexpr int64_t kResidentLds =
+    2 * kWave * (2 * sizeof(int64_t) + 2 * sizeof(int32_t)) +
+    kPieceVecs * sizeof(int64_t) + 64;
 // Copies over a plan take the resident walk while the checkpoint buffer is
 // smaller than this, the span or page-major walk from there on.  Buffers of
 // exactly the plan's rows, resident against the others, us per restore or
@@ -2143,7 +2155,9 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
     // request's first token, in 32.
     const size_t lds = sizeof(int64_t) * (size_t(num_reqs) + 1 + kWavesPerBlock);
     // No more workgroups than the buffer holds pieces for.
-    int64_t wgs = int64_t(dev->cus) * kResidentBlocks;
+    int64_t per_cu = kCuLds / (int64_t(lds) + kResidentLds);
+    if (per_cu > kResidentBlocks) per_cu = kResidentBlocks;
+    int64_t wgs = int64_t(dev->cus) * per_cu;
     if (cap_rows < wgs * kWavesPerBlock) {
       const int64_t need =
           (cap_rows * g.row_pieces + kWavesPerBlock - 1) / kWavesPerBlock;

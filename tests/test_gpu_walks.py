@@ -246,3 +246,14 @@ def test_plan_of_fewer_requests_is_refused_untouched(name):
         assert kv.lumen_kv_ckpt_status(ws) == kv.LUMEN_ERR_INVALID_ARG
         assert (ws[two:] == 0x5A).all()
         assert (ck == 0x5A).all() and torch.equal(pool, was)
+
+
+@pytest.mark.parametrize("R", [1500, 2600, 4096])
+def test_resident_walk_where_its_lds_limits_the_grid(R):
+    """Requests whose prefixes leave a CU room for fewer workgroups: more
+    pieces than that grid takes in a round."""
+    shape = CacheShape(2, 2, 64, 4, HND)
+    nb, bt, bt2, s, e, src, dst = ranges_case(shape, R, R, 16, 9)
+    ref = oracle_path(shape, nb, src, bt, s, e, nb, dst.copy(), bt2)
+    got = gpu_path(shape, nb, src, bt, s, e, nb, dst, bt2, via="ranges")
+    assert_same(got, ref, f"R={R}")
