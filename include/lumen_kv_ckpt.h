@@ -175,9 +175,8 @@ int lumen_kv_ckpt_plan(const int32_t *d_start, const int32_t *d_end,
  *
  * Grid size.  The plan's row count lives in device memory, so the launch is
  * sized without it.  While ckpt_rows (or the row range of the _rows calls)
- * is less than 128 MiB of rows and num_reqs at most
- * LUMEN_KV_CKPT_RANGES_MAX_REQS, the grid is what the chip holds and strides
- * over the rows that exist.  From there on it has 384 wavefronts per CU, or
+ * is less than 128 MiB of rows and num_reqs at most 1,024, the grid is what
+ * the chip holds and strides over the rows that exist.  From there on it has 384 wavefronts per CU, or
  * 768 when a (row, layer) unit is shorter than 4 KiB
  * (LUMEN_KV_CKPT_WAVES_PER_CU in the environment overrides both), but never
  * more than one per (row, layer) unit that ckpt_rows could hold, nor more

@@ -52,6 +52,7 @@
 #include <stdlib.h>
 
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "lumen_kv_ckpt.h"
@@ -836,6 +837,27 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
     return hdr->num_reqs == R ? narrow(hdr->total_rows) : 0;
   };
 
+  // The plan's prefix and starts into LDS, by kThreads threads, four of each
+  // in flight per thread: one after another, their trips to L2 add up.
+  auto load_plan = [&](auto threads, int me) {
+    constexpr int kThreads = decltype(threads)::value, kLoads = 4;
+    for (int32_t i0 = 0; i0 < R; i0 += kThreads * kLoads) {
+      int32_t p[kLoads], s[kLoads];
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        const int32_t i = min(i0 + j * kThreads + me, R - 1);
+        p[j] = int32_t(ws_prefix[i]);
+        s[j] = start[i];
+      }
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        const int32_t i = min(i0 + j * kThreads + me, R - 1);
+        prefix[i] = p[j];
+        first_tok[i] = s[j];
+      }
+    }
+  };
+
   // Table t of the workgroup, by one wavefront.
   auto build = [&](int32_t t, int32_t total) {
     const int32_t row_a = int32_t(min(g.row_lo, int64_t(total)));
@@ -907,10 +929,7 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
       } else {
         total = plan_total();
         if (hdr->num_reqs == R)
-          for (int32_t i = lane; i < R; i += kWave) {
-            prefix[i] = int32_t(ws_prefix[i]);
-            first_tok[i] = start[i];
-          }
+          load_plan(std::integral_constant<int, kWave>(), lane);
         else if (blockIdx.x == 0)
           record_error(err, LUMEN_ERR_INVALID_ARG);
       }
@@ -935,10 +954,7 @@ __attribute__((amdgpu_waves_per_eu(8))) void resident_copy_kernel(
     } else {
       total = plan_total();
       if (hdr->num_reqs == R)
-        for (int32_t i = tid; i < R; i += kBlockThreads) {
-          prefix[i] = int32_t(ws_prefix[i]);
-          first_tok[i] = start[i];
-        }
+        load_plan(std::integral_constant<int, kBlockThreads>(), tid);
       else if (blockIdx.x == 0 && wave == 0)
         record_error(err, LUMEN_ERR_INVALID_ARG);
       __syncthreads();
@@ -1816,6 +1832,15 @@ constexpr int64_t kResidentLds =
 // 58.3, 380 MB (head-major, fp32) 268 against 258.  Small steps into a larger
 // arena gain in both (23 MB arena: 17.6 to 16.0).
 constexpr int64_t kResidentMaxBytes = int64_t(128) << 20;
+// And while the plan has at most this many requests: every workgroup of the
+// resident walk loads all their prefixes, the span walk searches them in
+// place.  One token per request into a buffer of the rows, us for a plan and
+// copy in each direction, resident / span: 256 requests (40 KiB rows) 22.8 /
+// 21.0, 1,024 47.1 / 46.4, 2,048 80.2 / 78.5; of 1 KiB rows 1,024 17.1 / 15.8,
+// 2,048 21.6 / 19.7, 4,096 34.1 / 28.6.  Into an arena of four steps, which a
+// plan of many requests does not leave room for below 128 MiB, 256 requests
+// (40 KiB) 22.8 / 25.5, 512 29.2 / 39.5.
+constexpr int32_t kResidentPlanMaxReqs = 1024;
 // Copies over the ranges are steps that append to an arena, whatever its
 // size, and take the resident walk: an 8-request step into a 256 MB arena
 // 7.5 us a copy against 26, 256 requests into half of a 1.1 GB arena 217 us
@@ -2139,8 +2164,9 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
        cap_bytes >= (ranges ? kRangesPageMinBytes : kResidentMaxBytes)) &&
       (!ranges || num_reqs <= kRangesPageMaxReqs);
   const bool resident =
-      !pages && (ranges || (max_waves == 0 && num_reqs <= kRangesMaxReqs &&
-                            cap_bytes < kResidentMaxBytes));
+      !pages &&
+      (ranges || (max_waves == 0 && num_reqs <= kResidentPlanMaxReqs &&
+                  cap_bytes < kResidentMaxBytes));
   if (ranges && pages) {
     // LDS: the token and page prefixes, [R + 1] each, and the wavefronts'
     // totals of both.

@@ -52,7 +52,7 @@ def ranges_case(shape, R, seed, max_tok=40, longest=9):
 
 
 @pytest.mark.parametrize("via", ["plan", "ranges"])
-@pytest.mark.parametrize("R", [1, 3, 64, 255, 256, 257, 700])
+@pytest.mark.parametrize("R", [1, 3, 64, 255, 256, 257, 700, 1024])
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_resident_walk_matches_oracle(name, R, via):
     shape = SHAPES[name]
@@ -164,12 +164,12 @@ def test_slow_path_copies_the_valid_rows(R):
         assert (got[1][n:] == 0x5A).all()
 
 
-def test_plan_of_many_requests_takes_the_span_walk():
-    """More requests than the resident walk takes: 4,097, pack and unpack of
-    a token-major and a head-major cache."""
+@pytest.mark.parametrize("R", [1025, 4096, 4097])
+def test_plan_of_many_requests_takes_the_span_walk(R):
+    """More requests than the resident walk takes over a plan, pack and unpack
+    of a token-major and a head-major cache."""
     for order in (NHD, HND):
         shape = CacheShape(2, 4, 64, 8, order)
-        R = 4097
         nb, bt, bt2, s, e, src, dst = ranges_case(shape, R, 9, 16, 3)
         ref = oracle_path(shape, nb, src, bt, s, e, nb, dst.copy(), bt2)
         got = gpu_path(shape, nb, src, bt, s, e, nb, dst, bt2, via="plan")
