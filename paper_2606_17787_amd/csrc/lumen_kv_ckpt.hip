@@ -13,8 +13,8 @@
 // (token row, layer): one unit is the K and V of one token in one layer,
 // 2*H*D*E bytes, contiguous on the checkpoint side.  Units are numbered in
 // checkpoint order, u = packed_row * L + layer, and the grid's wavefronts
-// take equal contiguous spans of [0, total_units), so every wavefront that
-// has one moves the same bytes whatever the mix of request lengths.  The
+// take contiguous spans of [0, total_units) that differ by a unit at most, so
+// every wavefront moves the same bytes whatever the mix of request lengths.  The
 // grid is oversubscribed (hundreds of wavefronts per CU, about one unit each
 // on a decode step): wavefronts that share a workload still run at very
 // different speeds on this chip, and short-lived ones let the hardware
@@ -540,15 +540,17 @@ __global__ __launch_bounds__(kBlockThreads) LUMEN_COPY_OCCUPANCY void copy_rows_
     return;
   }
   const int64_t units = (row_b - row_a) * L;
-  // Wavefront gw's span: every wavefront that has one gets as many units, so
-  // that a plan which does not fill the buffer keeps the first wavefronts of
-  // the grid busy and the idle ones drain behind them.  Dealt evenly over the
-  // grid instead, 256 requests in half of their regions took 230 us a step
-  // against 224, a 196-row step in a 704 MB arena 52 against 48; full buffers
-  // are the same within 0.4%, or up to 4% faster (1 GB in 4 KiB units).
-  const int64_t per = (units + nw - 1) / nw;
-  int64_t u = row_a * L + gw * per;
-  const int64_t u_end = min(u + per, row_a * L + units);
+  // Wavefront gw's span: units / nw of them, and one more for the first
+  // wavefronts, so that a plan which does not fill the buffer keeps the first
+  // wavefronts of the grid busy and the idle ones drain behind them.  Dealt
+  // evenly over the grid instead (units * gw / nw), 256 requests in half of
+  // their regions took 230 us a step against 224, a 196-row step in a 704 MB
+  // arena 52 against 48, and the two 64-bit divisions per wavefront cost 12%
+  // where units are 2 KiB; with all spans rounded up to the same length, whole
+  // contexts left wavefronts idle (406 MB, pack and unpack: 303 us against 294).
+  const int64_t per = units / nw, longer = units - per * nw;
+  int64_t u = row_a * L + gw * per + min(gw, longer);
+  const int64_t u_end = u + per + (gw < longer ? 1 : 0);
   if (u >= u_end) return;
 
   // First token row of the span and its request.

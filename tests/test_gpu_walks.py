@@ -257,3 +257,29 @@ def test_resident_walk_where_its_lds_limits_the_grid(R):
     ref = oracle_path(shape, nb, src, bt, s, e, nb, dst.copy(), bt2)
     got = gpu_path(shape, nb, src, bt, s, e, nb, dst, bt2, via="ranges")
     assert_same(got, ref, f"R={R}")
+
+
+@pytest.mark.parametrize("workgroups", [1, 3, 7])
+@pytest.mark.parametrize("name", ["unit-258", "layers-per-piece-hnd"])
+def test_span_walk_of_many_units_per_wavefront(name, workgroups):
+    """Spans of several rows that cross requests, some a unit longer than the
+    others: a grid of a few wavefronts (the copies to and from host memory)."""
+    shape = SHAPES[name]
+    R = 23
+    nb, bt, bt2, s, e, src, dst = ranges_case(shape, R, workgroups, 40, 9)
+    total = int((e - s).sum())
+    ref = oracle_path(shape, nb, src, bt, s, e, nb, dst.copy(), bt2)
+    ws = kv.new_workspace(R, dev())
+    kv.lumen_kv_ckpt_plan(h2d(s), h2d(e), ws)
+    host = torch.zeros(total * shape.token_row_bytes, dtype=torch.uint8,
+                       pin_memory=True)
+    kv.lumen_kv_ckpt_pack_to_host_direct(shape, nb, h2d(src), h2d(bt), ws,
+                                         host, workgroups=workgroups)
+    torch.cuda.synchronize()
+    assert np.array_equal(host.numpy(), ref[1].view(np.uint8).reshape(-1))
+    d = h2d(dst)
+    kv.lumen_kv_ckpt_unpack_from_host_direct(shape, nb, d, h2d(bt2), ws, host,
+                                             workgroups=workgroups)
+    assert kv.lumen_kv_ckpt_status(ws) == 0
+    assert np.array_equal(d.cpu().numpy().view(np.uint8),
+                          ref[2].view(np.uint8))
