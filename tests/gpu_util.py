@@ -10,6 +10,9 @@ import oracle
 import paper_2606_17787_amd.kvckpt as kv
 
 SENTINEL = 0x5A
+# Requests of a plan from which on its copies take the span walk, however
+# small they are.
+SPAN_REQS = 1025
 
 
 def dev():
@@ -36,19 +39,39 @@ def d2h_words(t: torch.Tensor, elem_bytes: int) -> np.ndarray:
     return t.cpu().numpy().view(_WORD[elem_bytes])
 
 
+def pad_requests(s, e, req_row_base, *tables):
+    """The same requests and empty ones behind them, SPAN_REQS in all."""
+    more = max(0, SPAN_REQS - len(s))
+
+    def pad(a, v, dtype):
+        if a is None:
+            return None
+        a = np.asarray(a, dtype)
+        return np.concatenate([a, np.full((more,) + a.shape[1:], v, dtype)])
+
+    return (pad(s, 0, np.int32), pad(e, 0, np.int32),
+            pad(req_row_base, 0, np.int64),
+            *[pad(t, -1, np.int32) for t in tables])
+
+
 def gpu_path(shape, nb_src, src_pool, bt, s, e, nb_dst=None, dst_pool=None,
              bt_dst=None, row_base=0, req_row_base=None, ckpt_rows=None,
              in_place=False, via="plan"):
     """Plan + pack (+ unpack) on the GPU.  Returns (status, ckpt, dst_pool)
     as host arrays (dst_pool None when no unpack was asked for).  in_place:
-    the unpack writes into the pool the pack read from.  via="plan": the
-    plan kernel into a workspace, then the copies over it; via="ranges":
-    the one-launch copies that read the ranges themselves."""
+    the unpack writes into the pool the pack read from.  via="plan":
+    the plan kernel into a workspace, then the copies over it; via="ranges":
+    the one-launch copies that read the ranges themselves; via="span": as
+    "plan", with so many empty requests behind the others that the copies
+    take the span walk."""
     s = np.asarray(s, np.int32)
     e = np.asarray(e, np.int32)
-    R = s.shape[0]
     if ckpt_rows is None:
         ckpt_rows = int(np.maximum(e.astype(np.int64) - s, 0).sum()) + row_base
+    if via == "span":
+        s, e, req_row_base, bt, bt_dst = pad_requests(s, e, req_row_base, bt,
+                                                      bt_dst)
+    R = s.shape[0]
     row_elems = shape.token_row_elems
     eb = shape.elem_bytes
     ck_h = np.full(max(ckpt_rows, 0) * row_elems, SENTINEL, _WORD[eb])
@@ -70,7 +93,7 @@ def gpu_path(shape, nb_src, src_pool, bt, s, e, nb_dst=None, dst_pool=None,
                                            d_e, ck, status, row_base, rb)
         st = int(status.item())
     else:
-        assert via == "plan", via
+        assert via in ("plan", "span"), via
         ws = kv.new_workspace(R, dev())
         kv.lumen_kv_ckpt_plan(d_s, d_e, ws, row_base, rb)
         kv.lumen_kv_ckpt_pack(shape, nb_src, src, d_bt, ws, ck)

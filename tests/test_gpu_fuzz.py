@@ -2,8 +2,8 @@
 (layers, heads, head_dim, block size, element width, NHD or HND), a request
 count, block tables, token ranges (empty ones included), the plan mode
 (packed from a row base, or per-request rows) and a grid size, then checks
-pack, unpack, windowed packs, the direct host copy and the one-launch copies
-that read the ranges element by element.
+pack, unpack and windowed packs in both walks over a plan, the direct host
+copy and the one-launch copies that read the ranges element by element.
 One configuration in eight plants an error (a page past the table, or a
 block id outside the pool); then only the status is compared, since the GPU
 still copies the rows that are fine while the oracle writes nothing."""
@@ -16,7 +16,7 @@ import paper_2606_17787_amd.kvckpt as kv
 from paper_2606_17787_amd import workloads as W
 from paper_2606_17787_amd.workloads import CacheShape, HND, NHD
 
-from gpu_util import SENTINEL, d2h_words, dev, h2d
+from gpu_util import SENTINEL, d2h_words, dev, h2d, pad_requests
 
 pytestmark = pytest.mark.gpu
 
@@ -121,6 +121,23 @@ def test_random_configuration_matches_oracle(seed):
     assert kv.lumen_kv_ckpt_status(ws) == 0
     assert np.array_equal(d2h_words(d_dst, eb), want_dst)
 
+    # the span walk: the same plan with empty requests behind the others
+    s2, e2, base2, bt_p, bt2_p = pad_requests(s, e, base, bt, bt2)
+    ws2 = kv.new_workspace(len(s2), dev())
+    kv.lumen_kv_ckpt_plan(h2d(s2), h2d(e2), ws2,
+                          0 if per_request else row_base,
+                          None if base2 is None else h2d(base2))
+    ck_s = h2d(np.full(max(ck_rows, 1) * re_, SENTINEL, WORD[eb]))
+    d_dst_s = h2d(dst)
+    kv.lumen_kv_ckpt_pack(shape, nb, d_src, h2d(bt_p), ws2,
+                          ck_s[:ck_rows * re_])
+    kv.lumen_kv_ckpt_unpack(shape, nb, d_dst_s, h2d(bt2_p), ws2,
+                            ck_s[:ck_rows * re_])
+    assert kv.lumen_kv_ckpt_status(ws2) == 0
+    assert np.array_equal(
+        d2h_words(ck_s[:ck_rows * re_], eb).reshape(-1, re_), want_ck)
+    assert np.array_equal(d2h_words(d_dst_s, eb), want_dst)
+
     # the direct copy into pinned host memory, on a drawn grid size
     host = torch.empty((ck_rows * re_ * eb,), dtype=torch.uint8,
                        pin_memory=True)
@@ -139,16 +156,20 @@ def test_random_configuration_matches_oracle(seed):
     if not per_request and total:
         k = int(rng.integers(1, total + 1))
         kv.lumen_kv_ckpt_plan(d_s, d_e, ws, row_base)
-        parts = []
-        for lo in range(0, total, k):
-            hi = min(lo + k, total)
-            win = torch.zeros((hi - lo) * re_, dtype=ck.dtype, device=dev())
-            kv.lumen_kv_ckpt_pack_rows(shape, nb, d_src, d_bt, ws, lo, hi,
-                                       win, ckpt_first_row=row_base + lo)
-            parts.append(win)
-        assert kv.lumen_kv_ckpt_status(ws) == 0
-        got = np.concatenate([d2h_words(p, eb) for p in parts])
-        assert np.array_equal(got.reshape(-1, re_), want_ck[row_base:])
+        # (through the resident walk and, with the empty requests, the span
+        # walk)
+        for w, table in ((ws, d_bt), (ws2, h2d(bt_p))):
+            parts = []
+            for lo in range(0, total, k):
+                hi = min(lo + k, total)
+                win = torch.zeros((hi - lo) * re_, dtype=ck.dtype,
+                                  device=dev())
+                kv.lumen_kv_ckpt_pack_rows(shape, nb, d_src, table, w, lo, hi,
+                                           win, ckpt_first_row=row_base + lo)
+                parts.append(win)
+            assert kv.lumen_kv_ckpt_status(w) == 0
+            got = np.concatenate([d2h_words(p, eb) for p in parts])
+            assert np.array_equal(got.reshape(-1, re_), want_ck[row_base:])
 
 
 def draw_larger(seed):
@@ -176,9 +197,10 @@ def draw_larger(seed):
 @pytest.mark.parametrize("seed", range(12))
 def test_larger_random_shape_matches_oracle(seed):
     """Pack and restore of a serving-sized random shape, in the packed or
-    the per-request row mode, against the oracle.  At these sizes the copy
-    grid's spans cover several units and cross request boundaries, and the
-    unit sizes fall on both sides of the grid's 4 KiB threshold."""
+    the per-request row mode, against the oracle.  At these sizes the span
+    walk's spans cover several units and cross request boundaries, the unit
+    sizes fall on both sides of its grid's 4 KiB threshold, and the
+    checkpoints on both sides of the size from which plans take it."""
     from gpu_util import assert_same, gpu_path, oracle_path
     rng, shape, R, nb, pages, s, e = draw_larger(seed)
     cols = int(pages.max()) + int(rng.integers(0, 3))
@@ -203,6 +225,6 @@ def test_larger_random_shape_matches_oracle(seed):
         kw = dict(row_base=int(rng.integers(0, 5)))
     args = (shape, nb, src, bt, s, e, nb, dst, bt2)
     ref = oracle_path(*args, **kw)
-    for via in ("plan", "ranges"):
+    for via in ("plan", "ranges", "span"):
         assert_same(gpu_path(*args, **kw, via=via), ref,
                     f"seed {seed} via {via}: {shape}, {R} requests")

@@ -14,13 +14,16 @@ from paper_2606_17787_amd import workloads as W
 from paper_2606_17787_amd.workloads import CacheShape, HND, NHD
 
 from gpu_util import (SENTINEL, assert_same, gpu_path, oracle_path, h2d,
-                      d2h16, dev)
+                      d2h16, dev, pad_requests)
 
 pytestmark = pytest.mark.gpu
 
 # The two ways to run a plan's copies: the plan kernel into a workspace and
 # the copies over it, or the one-launch copies that read the ranges.
 VIAS = ["plan", "ranges"]
+# And the span walk of plans of many requests or large checkpoints, which small
+# copies reach by empty requests behind their own.
+WALKS = VIAS + ["span"]
 
 
 def test_smoke():
@@ -107,10 +110,10 @@ def test_prepared_calls_match_the_oracle(via):
 def test_tp8_shape_small_checkpoints(which):
     """Requests of the 70B TP=8 shard's shape (80 layers, one KV head: units
     of 512 bytes) with checkpoint buffers sized to their rows, 16 KB to
-    200 MB, where the copy grid is bounded by one wavefront per 4 KiB of
-    checkpoint rather than one per unit: the full pack, the same rows
-    through a window (the token-major walk) and the restore into a second,
-    fragmented pool, against the oracle."""
+    200 MB, on both sides of the size up to which copies take the resident
+    walk: the full pack, the same rows through a window (token by token at
+    every size) and the restore into a second, fragmented pool, against the
+    oracle."""
     w = W.c4_llama70b_tp8()
     sh = w.shape
     ctx = w.ends[0].astype(np.int64)
@@ -193,7 +196,7 @@ def _case(rng, shape, R, max_tok, incremental, nb_extra=7):
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: f"L{s.num_layers}H{s.num_kv_heads}D{s.head_dim}bs{s.block_size}{s.order}e{s.elem_bytes}")
 @pytest.mark.parametrize("incremental", [False, True])
-@pytest.mark.parametrize("via", VIAS)
+@pytest.mark.parametrize("via", WALKS)
 def test_random_shapes(shape, incremental, via):
     rng = np.random.default_rng(zlib.crc32(f"{shape}{incremental}".encode()))
     for R, max_tok in ((1, 5), (3, 40), (17, 100), (70, 30)):
@@ -214,7 +217,7 @@ def test_random_shapes(shape, incremental, via):
                     f"R={R} per-request")
 
 
-@pytest.mark.parametrize("via", VIAS)
+@pytest.mark.parametrize("via", WALKS)
 def test_empty_plan_and_all_empty_ranges(via):
     shape = CacheShape(2, 2, 64, 16, NHD)
     rng = np.random.default_rng(5)
@@ -246,7 +249,7 @@ ERROR_CASES = [
 
 
 @pytest.mark.parametrize("case", range(len(ERROR_CASES)))
-@pytest.mark.parametrize("via", VIAS)
+@pytest.mark.parametrize("via", WALKS)
 def test_device_error_codes_match_oracle(case, via):
     s, e, bt, rows, base, rb = ERROR_CASES[case]
     shape = CacheShape(2, 2, 8, 4, NHD)
@@ -268,9 +271,9 @@ def test_device_error_codes_match_oracle(case, via):
     assert st_g == kv.LUMEN_OK
 
 
-# One shape per walk of the copy kernels: 32-byte token runs (the full pack
-# takes the page-major walk), 1 KiB runs (token-major walk) and a head-major
-# cache.
+# Token-major caches of 32-byte runs (which a process can have packed page by
+# page at any size) and of 1 KiB runs, and a head-major cache; each through the
+# resident walk over a plan and over the ranges, and through the span walk.
 ERROR_WALK_SHAPES = {
     "nhd-page-major": CacheShape(2, 2, 8, 4, NHD),
     "nhd-token-major": CacheShape(2, 8, 64, 4, NHD),
@@ -301,12 +304,12 @@ def _valid_token_rows(shape, nb, bt, s, e, rows, base, rb):
 
 @pytest.mark.parametrize("walk", list(ERROR_WALK_SHAPES))
 @pytest.mark.parametrize("case", range(len(ERROR_CASES)))
-@pytest.mark.parametrize("via", VIAS)
+@pytest.mark.parametrize("via", WALKS)
 def test_error_inputs_still_copy_every_valid_row(case, walk, via):
     """On data-dependent errors only the offending token rows are skipped:
     every other row of the pack equals the oracle's pack of that token
     alone, rows no valid token names keep their sentinel, and the unpack
-    writes exactly the valid tokens' slots, for each walk of the kernels."""
+    writes exactly the valid tokens' slots, in every walk of the kernels."""
     s, e, bt, rows, base, rb = ERROR_CASES[case]
     shape = ERROR_WALK_SHAPES[walk]
     nb = 8
@@ -332,6 +335,8 @@ def test_error_inputs_still_copy_every_valid_row(case, walk, via):
                           ckpt=np.zeros((rows + 8, shape.token_row_elems),
                                         np.uint16), ckpt_rows=rows)
 
+    if via == "span":
+        s, e, rb, bt = pad_requests(s, e, rb, bt)
     ws = kv.new_workspace(len(s), dev())
     d_rb = None if rb is None else h2d(np.asarray(rb, np.int64))
     d_s, d_e, d_bt = h2d(s), h2d(e), h2d(bt)
@@ -366,7 +371,7 @@ def test_error_inputs_still_copy_every_valid_row(case, walk, via):
 
 
 @pytest.mark.parametrize("walk", list(ERROR_WALK_SHAPES))
-@pytest.mark.parametrize("via", VIAS)
+@pytest.mark.parametrize("via", WALKS)
 def test_ranges_past_the_unit_limit_copy_nothing(walk, via):
     """Ranges holding more (token row, layer) units than one launch walks
     (LUMEN_KV_CKPT_MAX_UNITS): ends of INT32_MAX on 1,024 requests are
@@ -390,7 +395,7 @@ def test_ranges_past_the_unit_limit_copy_nothing(walk, via):
 
 
 @pytest.mark.parametrize("walk", list(ERROR_WALK_SHAPES))
-@pytest.mark.parametrize("via", VIAS)
+@pytest.mark.parametrize("via", WALKS)
 def test_long_invalid_ranges_still_copy_their_valid_rows(walk, via):
     """Ranges far past their block tables but inside the unit limit: a
     range of 2^20 tokens whose first 12 lie in its table, and one ending at
@@ -418,6 +423,8 @@ def test_long_invalid_ranges_still_copy_their_valid_rows(walk, via):
     assert oracle.unpack(shape, nb, want_dst, bt[:1], [0], [n_ok],
                          ck_in[:n_ok]) == oracle.OK
 
+    if via == "span":
+        s, e, _, bt = pad_requests(s, e, None, bt)
     d_s, d_e, d_bt = h2d(s), h2d(e), h2d(bt)
     ck = h2d(np.full(rows * shape.token_row_elems, SENTINEL, np.uint16))
     ws = kv.new_workspace(len(s), dev())
@@ -727,7 +734,7 @@ def test_range_copies_on_two_streams_at_once():
     """The one-launch copies hold no state between calls: two of them in
     flight at once on two streams, each with its own status word, both
     equal the oracle."""
-    shape = CacheShape(4, 8, 128, 16, NHD)  # 4 KiB units: two spans a wave
+    shape = CacheShape(4, 8, 128, 16, NHD)  # 4 KiB units: a piece each
     rng = np.random.default_rng(909)
     cases = []
     for R, max_tok in ((37, 90), (11, 200)):
@@ -763,7 +770,7 @@ def test_range_copies_on_two_streams_at_once():
 @pytest.mark.parametrize("R", [700, 4096])
 def test_many_requests_with_long_units(R):
     """Thousands of requests over 4 KiB units: the one-launch copies then
-    scan several requests per thread and copy two spans per wavefront;
+    scan several requests per thread, and a plan's copies take the span walk;
     packed and per-request rows, both paths, against the oracle."""
     shape = CacheShape(2, 8, 128, 4, NHD)  # 2*8*128*2 = 4 KiB units
     rng = np.random.default_rng(R)

@@ -17,7 +17,8 @@ import paper_2606_17787_amd.kvckpt as kv
 from paper_2606_17787_amd import workloads as W
 from paper_2606_17787_amd.workloads import CacheShape, HND, NHD
 
-from gpu_util import assert_same, dev, gpu_path, h2d, oracle_path
+from gpu_util import (assert_same, d2h_words, dev, gpu_path, h2d,
+                      oracle_path)
 
 pytestmark = pytest.mark.gpu
 
@@ -135,7 +136,7 @@ def test_one_long_request_among_many(R, via):
     assert_same(got, ref, f"R={R} {via}")
 
 
-@pytest.mark.parametrize("R", [2, 256, 300, 4096])
+@pytest.mark.parametrize("R", [2, 256, 300, 1024, 4096])
 def test_slow_path_copies_the_valid_rows(R):
     """More rows than the 32-bit path takes (2^30 in all), of which only the
     first lie in their block table: the valid rows of every request are
@@ -149,19 +150,78 @@ def test_slow_path_copies_the_valid_rows(R):
     nb = 2 * R
     bt = rng.permutation(nb).astype(np.int32).reshape(R, cols)
     src = W.random_bits(rng, shape.pool_elems(nb))
-    rows = R // 2 + bs * cols + 4  # the long request's rows push the rest out
+    # (the long request's rows push the rest out)
+    rows = R // 2 + bs * cols + 8192
     valid = np.ones(R, np.int32)
     valid[R // 2] = bs * cols
     st, want = oracle.pack(shape, nb, src, bt[:R // 2 + 1], s[:R // 2 + 1],
                            valid[:R // 2 + 1])
     assert st == 0
     st_o = kv.LUMEN_ERR_CAPACITY if R // 2 + 1 < R else kv.LUMEN_ERR_RANGE
-    for via in ("plan", "ranges"):
+    for via in ("plan", "ranges") if R <= 1024 else ("ranges",):
         got = gpu_path(shape, nb, src, bt, s, e, ckpt_rows=rows, via=via)
         assert got[0] == st_o
         n = R // 2 + bs * cols
         assert np.array_equal(got[1][:n], want)
         assert (got[1][n:] == 0x5A).all()
+
+
+@pytest.mark.parametrize("via", ["plan", "window", "ranges"])
+@pytest.mark.parametrize("R", [3, 300])
+@pytest.mark.parametrize("name", ["layers-per-piece", "layers-per-piece-hnd",
+                                  "unit-258", "slices-hnd", "unit-2"])
+def test_slow_path_in_both_directions(name, R, via):
+    """Pack and unpack of more than 2^30 rows, all but a few past their block
+    table (RANGE): pieces of whole layers and slices of one, both orders, the
+    whole plan and a window of its rows."""
+    shape = SHAPES[name]
+    bs, cols = shape.block_size, 3
+    rng = np.random.default_rng(R + len(name))
+    s = rng.integers(0, bs * cols, R).astype(np.int32)
+    e = np.minimum(s + rng.integers(0, 4, R), bs * cols).astype(np.int32)
+    s[-1], e[-1] = bs * cols - 2, 2**30 + 500
+    e_ok = e.copy()
+    e_ok[-1] = bs * cols  # what lies in the table
+    rows = int((e_ok - s).sum())
+    # (they size the grid that walks the invalid rows)
+    spare = min(8192, (32 << 20) // shape.token_row_bytes)
+    nb = R * cols + 2
+    bt, bt2 = (rng.permutation(nb)[:R * cols].reshape(R, cols)
+               .astype(np.int32) for _ in range(2))
+    src = W.random_words(rng, shape.pool_elems(nb), shape.elem_bytes)
+    dst = W.random_words(rng, shape.pool_elems(nb), shape.elem_bytes)
+    if via != "window":
+        ref = oracle_path(shape, nb, src, bt, s, e_ok, nb, dst.copy(), bt2)
+        got = gpu_path(shape, nb, src, bt, s, e, nb, dst, bt2, via=via,
+                       ckpt_rows=rows + spare)
+        assert ref[0] == 0 and got[0] == kv.LUMEN_ERR_RANGE
+        assert np.array_equal(got[1][:rows], ref[1])
+        assert (got[1][rows:] == 0x5A).all()
+        assert np.array_equal(got[2], ref[2])
+        return
+    lo, hi = 2, rows + spare  # the first rows are not copied
+    d_src, d_dst = h2d(src), h2d(dst)
+    ws = kv.new_workspace(R, dev())
+    kv.lumen_kv_ckpt_plan(h2d(s), h2d(e), ws)
+    win = torch.full(((hi - lo) * shape.token_row_elems,), 0x5A,
+                     dtype=d_src.dtype, device=dev())
+    kv.lumen_kv_ckpt_pack_rows(shape, nb, d_src, h2d(bt), ws, lo, 2**40, win,
+                               ckpt_first_row=lo)
+    kv.lumen_kv_ckpt_unpack_rows(shape, nb, d_dst, h2d(bt2), ws, lo, 2**40,
+                                 win, ckpt_first_row=lo)
+    assert kv.lumen_kv_ckpt_status(ws) == kv.LUMEN_ERR_RANGE
+    st, want, _ = oracle_path(shape, nb, src, bt, s, e_ok)
+    got = d2h_words(win, shape.elem_bytes).reshape(hi - lo, -1)
+    assert st == 0 and np.array_equal(got[:rows - lo], want[lo:])
+    assert (got[rows - lo:] == 0x5A).all()
+    s2, skip = s.copy(), lo  # the tokens of the rows from lo on
+    for r in range(R):
+        n = min(skip, int(e_ok[r] - s[r]))
+        s2[r] += n
+        skip -= n
+    want_dst = dst.copy()
+    assert oracle.unpack(shape, nb, want_dst, bt2, s2, e_ok, want[lo:]) == 0
+    assert np.array_equal(d2h_words(d_dst, shape.elem_bytes), want_dst)
 
 
 @pytest.mark.parametrize("R", [1025, 4096, 4097])
