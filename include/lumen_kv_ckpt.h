@@ -58,7 +58,8 @@
  * recovery restores, Sec. 4.3).
  *
  * Ownership and ordering.  Every buffer is allocated and owned by the
- * caller; the library allocates no device memory.  All calls are
+ * caller; the library allocates no device memory (and of host memory only the
+ * page that lumen_kv_ckpt_status says).  All calls are
  * asynchronous and stream-ordered on the hipStream_t passed as `stream`
  * (NULL is the null stream), except lumen_kv_ckpt_status, which
  * synchronises that stream.  A workspace must not be shared by calls that
@@ -245,8 +246,9 @@ int lumen_kv_ckpt_unpack(const lumen_kv_layout *layout, void *d_cache,
  * arena costs what it does into a buffer of its rows (8 requests, 65 rows:
  * 7.5 us).  Only a pack of a token-major cache with token runs of at most 512
  * bytes into 4 GiB of rows or more, for up to 2,048 requests, goes page by
- * page as lumen_kv_ckpt_pack does (its grid is then sized by ckpt_rows, and
- * it keeps token and page prefixes, 16 * (num_reqs + 5) bytes of LDS).
+ * page as lumen_kv_ckpt_pack does (its grid is then sized by ckpt_rows, so
+ * that small steps into such an arena take 50-80 us, and it keeps token and
+ * page prefixes, 16 * (num_reqs + 5) bytes of LDS).
  *
  * Status.  d_status is a caller-owned device int32, 4-byte aligned.  A call
  * only lowers it (atomic minimum) to the most negative code it records and
@@ -423,7 +425,8 @@ size_t lumen_kv_ckpt_marks_bytes(int64_t num_blocks);
  * d_marks: caller-owned device scratch of marks_bytes >=
  * lumen_kv_ckpt_marks_bytes(num_blocks) bytes, 16-byte aligned, cleared by
  * the call where it needs it (by a kernel, not a memset; a small call keeps
- * its bits on the chip); it may be NULL only if num_blocks is 0.  Calls sharing d_marks must not be in flight at the same time.
+ * its bits on the chip); it may be NULL only if num_blocks is 0.  Calls
+ * sharing d_marks must not be in flight at the same time.
  * Nothing in the cache or the checkpoint is read or written. */
 int lumen_kv_ckpt_validate_targets(const lumen_kv_layout *layout,
                                    const int32_t *d_block_tables,
@@ -464,7 +467,9 @@ int lumen_kv_draft_align(const int32_t *d_draft, int32_t draft_cols,
                          void *d_workspace, lumen_stream_t stream);
 
 /* Synchronises `stream`, then returns and clears the workspace's error word
- * (LUMEN_OK if no device-side error was recorded since the last plan). */
+ * (LUMEN_OK if no device-side error was recorded since the last plan).  The
+ * first call on a GPU allocates one 4 KiB page of pinned host memory, which
+ * receives the codes and is kept until the process ends. */
 int lumen_kv_ckpt_status(void *d_workspace, lumen_stream_t stream);
 
 /* Static string for a status code. */

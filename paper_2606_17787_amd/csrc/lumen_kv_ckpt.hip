@@ -7,39 +7,40 @@
 // alignment), the staging pipelines to and from pinned host memory, and the
 // C ABI.
 //
-// Work decomposition.  A checkpoint is a sequence of token rows, each
+// What is moved.  A checkpoint is a sequence of token rows, each
 // [L][2][H][D] elements of E bytes (E = 1, 2 or 4; the copy moves raw bits
-// and never looks at values).  The copy is split into units of
-// (token row, layer): one unit is the K and V of one token in one layer,
-// 2*H*D*E bytes, contiguous on the checkpoint side.  Units are numbered in
-// checkpoint order, u = packed_row * L + layer, and the grid's wavefronts
-// take contiguous spans of [0, total_units) that differ by a unit at most, so
-// every wavefront moves the same bytes whatever the mix of request lengths.  The
-// grid is oversubscribed (hundreds of wavefronts per CU, about one unit each
-// on a decode step): wavefronts that share a workload still run at very
-// different speeds on this chip, and short-lived ones let the hardware
-// dispatcher hand the remaining work to whichever CU frees a slot first,
-// where a grid of resident long-lived wavefronts ends on its slowest one.
-// Small checkpoints with short units get fewer, longer-lived wavefronts (at
-// least 4 KiB each, while that leaves 16 per CU), since there a wavefront
-// per unit makes wavefront dispatch the bound.
-// Inside its span a wavefront walks token rows in order: the
-// request, its block-table entry and the checkpoint row of each token are
-// wave-uniform and live in scalar registers; the 64 lanes then move the
-// token's units as 16-byte vectors.  On the checkpoint side those vectors
-// are one contiguous run; on the cache side they are runs of H*D*E bytes
-// (token-major cache) or D*E bytes (head-major cache), each a whole number
-// of 128-byte lines for the serving shapes, so every access is full-line and
-// no LDS staging is needed for the head-major transpose.
+// and never looks at values), as 16-byte vectors.  On the checkpoint side a
+// row is one contiguous run; on the cache side it is runs of H*D*E bytes
+// (token-major cache) or D*E bytes (head-major cache), each a whole number of
+// 128-byte lines for the serving shapes, so every access is full-line and no
+// LDS staging is needed for the head-major transpose.  Three walks share these
+// addresses and differ in how the rows are dealt to the chip:
 //
-// That is the span walk (copy_rows_kernel), for large copies over a plan and
-// for host memory.  Two others share its addresses:
-//   * the resident walk (resident_copy_kernel), for smaller copies and for
-//     those that read the token ranges themselves instead of a plan: a grid
-//     of what the chip holds strides over 4 KiB pieces of the rows that
-//     exist, however large the checkpoint buffer is;
-//   * the page-major pack (pack_pages_kernel), for large packs of token-major
+//   * The span walk (copy_rows_kernel): large copies over a plan, plans of
+//     many requests, and host memory.  The unit is a (token row, layer): the K
+//     and V of one token in one layer, 2*H*D*E bytes, contiguous on the
+//     checkpoint side.  Units are numbered in checkpoint order, u = packed_row
+//     * L + layer, and the grid's wavefronts take contiguous spans of [0,
+//     total_units) that differ by a unit at most, so every wavefront moves the
+//     same bytes whatever the mix of request lengths.  The grid is
+//     oversubscribed (hundreds of wavefronts per CU, about one unit each on a
+//     decode step): wavefronts that share a workload still run at very
+//     different speeds on this chip, and short-lived ones let the hardware
+//     dispatcher hand the remaining work to whichever CU frees a slot first,
+//     where a grid of resident long-lived wavefronts ends on its slowest one.
+//     Small checkpoints with short units get fewer, longer-lived wavefronts
+//     (at least 4 KiB each, while that leaves 16 per CU), since there a
+//     wavefront per unit makes wavefront dispatch the bound.  Inside its span
+//     a wavefront walks token rows in order: the request, its block-table
+//     entry and the checkpoint row of each token are wave-uniform and live in
+//     scalar registers; the 64 lanes then move the token's units.
+//   * The resident walk (resident_copy_kernel): smaller copies over a plan,
+//     and those that read the token ranges themselves instead of one.  A grid
+//     of what the chip holds strides over 4 KiB pieces of the rows that exist,
+//     however large the checkpoint buffer is.
+//   * The page-major pack (pack_pages_kernel): large packs of token-major
 //     caches with short token runs.
+//
 // Where they find their plan: a plan kernel has written it into a caller's
 // workspace (the row prefix of every request), or each workgroup scans the
 // token ranges into LDS before its wavefronts start, which saves the plan
@@ -399,8 +400,8 @@ __device__ __forceinline__ int row_status(bool past, int32_t entry,
   return LUMEN_OK;
 }
 
-// Where the span walk finds a token row's request, source token and
-// checkpoint row: in the plan that a plan kernel wrote into the workspace.
+// The span walk's position in the plan that a plan kernel wrote into the
+// workspace: a token row's request, source token and checkpoint row.
 struct WsWalk {
   const WsHeader *hdr;
   const int64_t *prefix;
@@ -1546,9 +1547,10 @@ __global__ __launch_bounds__(kBlockThreads) void validate_kernel(
 // of a page's entry.  Request r's pages go to threads [r << shift,
 // (r + 1) << shift), 64 of them or more.  us a call in a graph, two launches
 // against this one: 1 request of 126 pages 3.7 / 2.1, of 16384 54 / 4.5; 16
-// of 1024 in a pool of 131072 blocks 6.6 / 4.5, 16 of 128 3.8 / 2.4.  The
-// limits are what a wavefront per request and 16 entries per thread hold;
-// every call within them is faster here.
+// of 1024 in a pool of 131072 blocks 6.6 / 4.5, 16 of 128 3.8 / 2.4, 9 of
+// 1820 9.5 / 5.7 (64 threads a request), 16 of one page in the largest pool
+// 3.7 / 2.3.  The limits are what a wavefront per request and 16 entries per
+// thread (of 1024) hold; of 19 calls at and inside them none was slower here.
 constexpr int kSmallThreads = 1024;
 constexpr int64_t kSmallPool = 131072;     // 16 KiB of bits
 constexpr int32_t kSmallReqs = kSmallThreads / kWave;
@@ -1844,12 +1846,26 @@ constexpr int64_t kResidentMaxBytes = int64_t(128) << 20;
 // (40 KiB) 22.8 / 25.5, 512 29.2 / 39.5.
 constexpr int32_t kResidentPlanMaxReqs = 1024;
 // Copies over the ranges are steps that append to an arena, whatever its
-// size, and take the resident walk: an 8-request step into a 256 MB arena
-// 7.5 us a copy against 26, 256 requests into half of a 1.1 GB arena 217 us
-// a step against 221, into a buffer of exactly their rows 216 against 212,
-// 2 KiB units 286 against 424.  Only a pack of one-KV-head rows (page-major
-// below) of more than this keeps its own walk: there whole contexts are
-// packed, and 114 GB of them run at 6.2 TB/s page by page.
+// size, and take the resident walk.  Against a span walk over the ranges,
+// whose grid the buffer sizes, us for a pack and an unpack: 8 requests of 1-16
+// tokens into a 16-step arena 14.8 / 37.7, 256 of one token 31.7 / 62.5, 200
+// of 1-64 (2 KiB units) 277 / 411, whole contexts of 2.1 GB 1,608 / 1,619.  It
+// is the slower one where about 2,000 rows of 128 KiB fill the chip eight
+// times: 256 requests of 1-16 tokens 213-228 / 207-222, all of it in the pack,
+// whose workgroups, with the same share each, end between 79 and 103 us.  The
+// host does not know the rows, and what evens them out costs the small steps:
+// grids of 2 to 6 times as many workgroups, or as many again for the last
+// rounds (at best 1.5% of that step, for 2-4% of a step of 256 tokens).
+// Pieces dealt by ticket within a workgroup and shares rotated over the layers
+// did not help.
+//
+// Only a pack of one-KV-head rows (page-major below) of this size and more
+// keeps its own walk: there whole contexts are packed.  us token by token /
+// page by page, 40 KiB rows: contexts of 0.25 GiB 95 / 101, 1 GiB 385 / 400,
+// 2 GiB 782 / 780, 3.9 GiB 1,583 / 1,560, 8 GiB 3,114 / 2,985, 16 GiB 6,407 /
+// 5,499; a step of 256 requests into an arena of 4.2 GiB 31 / 82 (1-16 tokens
+// each) and 7 / 71 (one).  Contexts alone would put the line at 2 GiB, steps
+// far above: between the two, contexts lose 1.5% at most.
 constexpr int64_t kRangesPageMinBytes = int64_t(4) << 30;
 constexpr size_t kScratchBytes = ws_bytes(kNoAllocMaxReqs);
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
