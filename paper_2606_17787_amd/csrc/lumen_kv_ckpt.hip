@@ -232,6 +232,16 @@ __device__ __forceinline__ void record_error(int32_t *err, int code) {
   if ((threadIdx.x & (kWave - 1)) == 0) atomicMin(err, code);
 }
 
+// The same for a wave-uniform code, where it is worse than the wavefront's
+// worst so far: a malformed call's 2^30 invalid rows, an atomic on one word
+// each, held the GPU for 12 s.
+__device__ __forceinline__ void record_worse(int32_t *err, int code,
+                                             int &worst) {
+  if (code >= worst) return;
+  worst = code;
+  record_error(err, code);
+}
+
 // Byte offset, relative to (block, slot) of layer 0 / K, of vector `vv` of a
 // token's checkpoint row segment (vv counts 16-byte vectors from the start of
 // the row: layer-major, then K/V, then head, then dim).
@@ -566,6 +576,7 @@ __global__ __launch_bounds__(kBlockThreads) LUMEN_COPY_OCCUPANCY void copy_rows_
   }
   bool past;
   int32_t b = block_tables[entry_index(r, t, g, past)];
+  int worst = LUMEN_OK;  // recorded by this wavefront
 
   while (true) {
     const int32_t nl = int32_t(min(int64_t(g.num_layers - l0), u_end - u));
@@ -596,7 +607,7 @@ __global__ __launch_bounds__(kBlockThreads) LUMEN_COPY_OCCUPANCY void copy_rows_
     const int32_t b2 = block_tables[entry_index(r2, t2, g, past2)];
 
     if (code != LUMEN_OK) {
-      record_error(err, code);
+      record_worse(err, code, worst);
     } else {
       copy_segment<kPack, kHeadMajor>(src, dst, cache_tok, ckpt_off,
                                       uint32_t(l0) * uint32_t(g.unit_vecs),
@@ -1352,6 +1363,7 @@ pack_pages_kernel(const uint8_t *__restrict__ cache, uint8_t *__restrict__ ckpt,
   const int64_t units = total_items * groups;
   const int32_t tok = g.slot_bytes;  // H*D*E
   const int32_t vpt = tok / 16;
+  int worst = LUMEN_OK;  // recorded by this wavefront
   for (int64_t u = gw; u < units; u += nw) {
     const int64_t item = u / groups;
     const int32_t l_first = int32_t(u - item * groups) * G;
@@ -1373,15 +1385,15 @@ pack_pages_kernel(const uint8_t *__restrict__ cache, uint8_t *__restrict__ ckpt,
     const int32_t ta = int32_t(min(ta64, int64_t(nt)));
     const int32_t tb = int32_t(max(min(room, int64_t(nt)), int64_t(ta)));
     if (j >= g.bt_cols) {
-      record_error(err, LUMEN_ERR_RANGE);
+      record_worse(err, LUMEN_ERR_RANGE, worst);
       continue;
     }
     const int32_t b = block_tables[int64_t(r) * g.bt_cols + j];
     if (b < 0 || b >= g.num_blocks) {
-      record_error(err, LUMEN_ERR_BLOCK_ID);
+      record_worse(err, LUMEN_ERR_BLOCK_ID, worst);
       continue;
     }
-    if (ta > 0 || tb < nt) record_error(err, LUMEN_ERR_CAPACITY);
+    if (ta > 0 || tb < nt) record_worse(err, LUMEN_ERR_CAPACITY, worst);
     const int64_t blk = int64_t(b) * g.block_bytes +
                         (t_lo - j * g.block_size) * int64_t(tok);
     const int32_t nv = tb * vpt;  // vectors of the K (or V) run to copy
