@@ -1995,6 +1995,14 @@ int current_device(DeviceInfo **info) {
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
+// The caller's stream.  hipStreamLegacy names the null stream and is passed on
+// as that: launches take the handle itself, but not every query of a stream
+// does (a status call on it crashed the process).
+hipStream_t as_stream(lumen_stream_t stream) {
+  const hipStream_t s = static_cast<hipStream_t>(stream);
+  return s == hipStreamLegacy ? nullptr : s;
+}
+
 // Takes an error that an earlier runtime call of this thread left pending
 // (the caller's, say a failed event query), so that the check after this
 // call's launches reports their own outcome only.
@@ -2176,7 +2184,7 @@ int launch_copy(bool pack, const lumen_kv_layout *lay, const void *src,
     if (pieces < waves) waves = pieces > 0 ? pieces : 1;
   }
   const unsigned blocks = unsigned((waves + kWavesPerBlock - 1) / kWavesPerBlock);
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  hipStream_t s = as_stream(stream);
   const uint8_t *in = static_cast<const uint8_t *>(src);
   uint8_t *out = static_cast<uint8_t *>(dst);
   const Timing tm = take_timing();  // a copy kernel is launched below
@@ -2494,7 +2502,7 @@ int lumen_kv_ckpt_plan(const int32_t *d_start, const int32_t *d_end,
   WsView v = ws_view(d_workspace, num_reqs);
   clear_pending_error();
   hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0,
-                     static_cast<hipStream_t>(stream), d_start, d_end,
+                     as_stream(stream), d_start, d_end,
                      num_reqs, row_base, d_req_row_base, v.hdr, v.prefix,
                      v.first_row, v.start, &v.hdr->err);
   return hipGetLastError() == hipSuccess ? LUMEN_OK : LUMEN_ERR_HIP;
@@ -2541,7 +2549,7 @@ int lumen_kv_ckpt_pack_noalloc(const lumen_kv_layout *layout,
   WsView v = ws_view(dev->scratch, num_reqs);
   clear_pending_error();
   hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0,
-                     static_cast<hipStream_t>(stream), d_start, d_end,
+                     as_stream(stream), d_start, d_end,
                      num_reqs, row_base, d_req_row_base, v.hdr, v.prefix,
                      v.first_row, v.start, d_status);
   if (hipGetLastError() != hipSuccess) return LUMEN_ERR_HIP;
@@ -2633,7 +2641,7 @@ int lumen_kv_ckpt_validate_targets(const lumen_kv_layout *layout,
   st = current_device(&dev);
   if (st != LUMEN_OK) return st;
   WsView v = ws_view(d_workspace, num_reqs);
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  hipStream_t s = as_stream(stream);
   const int64_t n16 = int64_t(need / 16);
   clear_pending_error();
   if (num_reqs <= kSmallReqs && layout->num_blocks <= kSmallPool &&
@@ -2680,8 +2688,8 @@ int lumen_kv_ckpt_pack_to_host(const lumen_kv_layout *layout,
   const int64_t row_bytes = int64_t(layout->num_layers) * 2 *
                             layout->num_kv_heads * layout->head_dim *
                             layout->elem_bytes;
-  hipStream_t ps = static_cast<hipStream_t>(pack_stream);
-  hipStream_t cs = static_cast<hipStream_t>(copy_stream);
+  hipStream_t ps = as_stream(pack_stream);
+  hipStream_t cs = as_stream(copy_stream);
   std::lock_guard<std::mutex> lock(dev->pipe_mu);
   st = pipe_events(dev, 2 * size_t(slots));
   if (st != LUMEN_OK) return st;
@@ -2729,8 +2737,8 @@ int lumen_kv_ckpt_unpack_from_host(const lumen_kv_layout *layout,
   const int64_t row_bytes = int64_t(layout->num_layers) * 2 *
                             layout->num_kv_heads * layout->head_dim *
                             layout->elem_bytes;
-  hipStream_t cs = static_cast<hipStream_t>(copy_stream);
-  hipStream_t us = static_cast<hipStream_t>(unpack_stream);
+  hipStream_t cs = as_stream(copy_stream);
+  hipStream_t us = as_stream(unpack_stream);
   std::lock_guard<std::mutex> lock(dev->pipe_mu);
   st = pipe_events(dev, 2 * size_t(slots));
   if (st != LUMEN_OK) return st;
@@ -2805,7 +2813,7 @@ int lumen_kv_draft_align(const int32_t *d_draft, int32_t draft_cols,
   int st = current_device(&dev);
   if (st != LUMEN_OK) return st;
   WsView v = ws_view(d_workspace, num_reqs);
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  hipStream_t s = as_stream(stream);
   clear_pending_error();
   if (num_reqs > 0) {
     // A workgroup per request while that many fit the chip at once, or where
@@ -2841,7 +2849,7 @@ int lumen_kv_draft_align(const int32_t *d_draft, int32_t draft_cols,
 int lumen_kv_ckpt_status(void *d_workspace, lumen_stream_t stream) {
   if (!d_workspace) return LUMEN_ERR_INVALID_ARG;
   if (!aligned16(d_workspace)) return LUMEN_ERR_MISALIGNED;
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  hipStream_t s = as_stream(stream);
   WsHeader *hdr = static_cast<WsHeader *>(d_workspace);
   int code = 0;
   if (status_by_kernel(&hdr->err, s, &code)) return code;
@@ -2889,8 +2897,8 @@ int lumen_kv_ckpt_offload(const void *d_src, void *h_dst, size_t bytes,
   DeviceInfo *dev = nullptr;
   int st = current_device(&dev);
   if (st != LUMEN_OK) return st;
-  hipStream_t p = static_cast<hipStream_t>(producer);
-  hipStream_t q = static_cast<hipStream_t>(side);
+  hipStream_t p = as_stream(producer);
+  hipStream_t q = as_stream(side);
   {
     // A wait captures the event's latest record at the time of the call, so
     // one event per device serves every call.
@@ -2911,8 +2919,8 @@ int lumen_kv_ckpt_stage_in(const void *h_src, void *d_dst, size_t bytes,
   DeviceInfo *dev = nullptr;
   int st = current_device(&dev);
   if (st != LUMEN_OK) return st;
-  hipStream_t q = static_cast<hipStream_t>(side);
-  hipStream_t c = static_cast<hipStream_t>(consumer);
+  hipStream_t q = as_stream(side);
+  hipStream_t c = as_stream(consumer);
   if (hipMemcpyAsync(d_dst, h_src, bytes, hipMemcpyHostToDevice, q) != hipSuccess)
     return LUMEN_ERR_HIP;
   std::lock_guard<std::mutex> lock(dev->event_mu);

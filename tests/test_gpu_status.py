@@ -1,6 +1,7 @@
 """lumen_kv_ckpt_status reads and clears the error word of its own workspace,
 also from more host threads at once than the library has words to receive
 codes in, each on a stream of its own."""
+import ctypes
 import threading
 
 import numpy as np
@@ -8,6 +9,7 @@ import pytest
 import torch
 
 import paper_2606_17787_amd.kvckpt as kv
+from paper_2606_17787_amd.workloads import CacheShape, NHD
 
 from gpu_util import dev, h2d
 
@@ -46,3 +48,32 @@ def test_every_thread_reads_its_own_word(threads):
     for i in range(threads):
         bad = kv.LUMEN_ERR_RANGE if i % 2 else kv.LUMEN_OK
         assert out[i] == [bad, kv.LUMEN_OK] * 5
+
+
+@pytest.mark.parametrize("handle", [0, 1, 2],
+                         ids=["null", "hipStreamLegacy", "hipStreamPerThread"])
+def test_streams_that_are_names(handle):
+    """Every entry point that takes a stream takes the runtime's named ones:
+    a plan, a pack over it and the status, on the handle itself."""
+    lib = kv.load_library()
+    shape = CacheShape(2, 2, 16, 4, NHD)
+    nb = 3
+    lay = kv.layout(shape, nb)
+    src = torch.arange(shape.pool_elems(nb), dtype=torch.int16, device=dev())
+    ck = torch.zeros(4 * shape.token_row_elems, dtype=torch.int16,
+                     device=dev())
+    bt = h2d(np.array([[2], [1]], np.int32))
+    s, e = h2d(np.array([0, 0], np.int32)), h2d(np.array([4, -1], np.int32))
+    ws = kv.new_workspace(2, dev())
+    torch.cuda.synchronize()
+    assert lib.lumen_kv_ckpt_plan(s.data_ptr(), e.data_ptr(), 2, 0, None,
+                                  ws.data_ptr(), handle) == 0
+    assert lib.lumen_kv_ckpt_pack(ctypes.byref(lay), src.data_ptr(),
+                                  bt.data_ptr(), 1, 2, ws.data_ptr(),
+                                  ck.data_ptr(), 4, handle) == 0
+    assert lib.lumen_kv_ckpt_status(ws.data_ptr(), handle) == \
+        kv.LUMEN_ERR_RANGE
+    assert lib.lumen_kv_ckpt_status(ws.data_ptr(), handle) == kv.LUMEN_OK
+    block = src.view(shape.num_layers, 2, nb, 4, -1)[:, :, 2]
+    assert torch.equal(ck.view(4, shape.num_layers, 2, -1),
+                       block.permute(2, 0, 1, 3))
